@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <string>
 #include <tuple>
@@ -890,6 +891,23 @@ size_t amer_task_bytes(int n) { return (sizeof(LsmTask) * (size_t)n + kAlign - 1
 size_t amer_result_bytes(int n) { return sizeof(double) * 2 * (size_t)n + sizeof(int32_t) * (size_t)(n + 1); }
 size_t amer_pinned_bytes(int n) { return amer_task_bytes(n) + amer_result_bytes(n); }
 
+// A pass of three or more options of at most 2^18 paths each runs its spills, Gram sums, factors and
+// (in a Greeks batch) adjoints in one launch each over all options: one such option leaves most
+// of the chip idle for as long as its serial steps take.  Other passes take one launch per option
+// and step.  Measured (us per call, a launch each / together): 30 options of 25,000 paths x 504
+// steps 7,413 / 3,717, 10 of 25,000 x 126 945 / 499; Greeks of 4 options of 131,072 x 252 1,956 /
+// 1,825, of 2^18 2,763 / 2,646, of 2^19 5,569 / 5,662, of 2 of 2^20 4,780 / 4,837 (a large option
+// fills the chip alone).
+constexpr int64_t kTogetherMin = 3;
+constexpr int64_t kTogetherPaths = (int64_t)1 << 18;
+
+bool run_together(const simr_option* opts, const std::vector<int64_t>& idx) {
+  if ((int64_t)idx.size() < kTogetherMin) return false;
+  for (int64_t i : idx)
+    if (opts[i].paths > kTogetherPaths) return false;
+  return true;
+}
+
 // American options by Longstaff-Schwartz: spill every option forward (which also clears its
 // zero words), precompute the Gram factors of every date, run the backward inductions (as many
 // options per cooperative launch as fit co-resident, each on its own blocks), finish all
@@ -897,7 +915,8 @@ size_t amer_pinned_bytes(int n) { return amer_task_bytes(n) + amer_result_bytes(
 // context's pinned buffer, at an offset that leaves amer_pinned_bytes(n) inside it).  Nothing is
 // synchronised; *coop tells collect_american_group how the induction ran.
 simr_status enqueue_american_group(simr_ctx* c, int scheme, const simr_option* opts, const AmerGroup& g,
-                                   bool want_beta, char* stage, hipStream_t s, bool* coop_out) {
+                                   bool want_beta, char* stage, hipStream_t s, bool* coop_out,
+                                   const std::function<void(int, LsmTask*)>& adj = nullptr) {
   const int n = (int)g.idx.size();
   if (stage < (char*)c->pinned || stage + amer_pinned_bytes(n) > (char*)c->pinned + c->pinned_bytes)
     return fail(SIMR_EINVAL, "internal: pinned staging too small");
@@ -908,16 +927,26 @@ simr_status enqueue_american_group(simr_ctx* c, int scheme, const simr_option* o
     if (st != SIMR_OK) return st;
     paths[k] = opts[g.idx[k]].paths;
   }
-  // first on the stream: the long forward passes hide the host's later enqueues (every launch
-  // is its own profile record)
-  for (int k = 0; k < n; ++k) {
-    const int64_t nz = kOptZeroWords + (k == n - 1 ? 16 : 0);  // the last one also clears the status
-    Prof pf(c, SIMR_PROF_SPILL, s);
-    SIMR_HIP(launch_forward_spill(scheme, d[k], g.b[k].xs, g.b[k].vs, g.zero + (size_t)k * kOptZeroWords, nz, s));
-  }
   std::vector<int> grids;
   std::vector<LsmLaunchSet> sets;
-  if (!c->lsm_per_date) sets = lsm_coop_plan(paths, c->num_cus, c->lsm_grid_max, &grids, 6, c->lsm_block);
+  auto plan = [&]() {
+    if (!c->lsm_per_date) sets = lsm_coop_plan(paths, c->num_cus, c->lsm_grid_max, &grids, 6, c->lsm_block);
+  };
+  bool together = run_together(opts, g.idx);
+  if (together) {
+    plan();
+    together = !sets.empty();
+  }
+  if (!together) {
+    // first on the stream: the long forward passes hide the plan and the host's later enqueues
+    // (every launch is its own profile record)
+    for (int k = 0; k < n; ++k) {
+      const int64_t nz = kOptZeroWords + (k == n - 1 ? 16 : 0);  // the last one also clears the status
+      Prof pf(c, SIMR_PROF_SPILL, s);
+      SIMR_HIP(launch_forward_spill(scheme, d[k], g.b[k].xs, g.b[k].vs, g.zero + (size_t)k * kOptZeroWords, nz, s));
+    }
+    plan();
+  }
   const bool coop = !sets.empty();
   // the task table: the cooperative launches' blocks, and the finish's partial rows
   LsmTask* ht = (LsmTask*)stage;
@@ -929,9 +958,12 @@ simr_status enqueue_american_group(simr_ctx* c, int scheme, const simr_option* o
       b0 += grids[k];
     }
   }
+  int32_t ngram = 0, nfac = 0;
   for (int k = 0; k < n; ++k) {
     const LsmBufs& b = g.b[k];
+    const simr_option& o = opts[g.idx[k]];
     LsmTask t;
+    std::memset(&t, 0, sizeof t);
     t.o = d[k];
     t.xs = b.xs;
     t.vs = b.vs;
@@ -943,16 +975,50 @@ simr_status enqueue_american_group(simr_ctx* c, int scheme, const simr_option* o
     t.flags = b.st.flags;
     t.block0 = block0[k];
     t.nblocks = coop ? grids[k] : b.nblk;
+    t.gram = b.gram;
+    t.rdt = o.r * o.T / o.steps;
+    t.chunks = lsm_gram_chunks(o.paths);
+    t.per_lane = lsm_gram_per_lane(o.paths);
+    t.spilln = b.nblk;
+    t.gram0 = ngram;
+    t.gramn = (o.steps - 1) * t.chunks;
+    t.fac0 = nfac;
+    t.facn = o.steps - 1;
+    ngram += t.gramn;
+    nfac += t.facn;
+    if (adj) adj(k, &t);
     ht[k] = t;
   }
+  int32_t nspill = 0;
+  if (together) {  // the spill's blocks in descending steps: the longest chains start first
+    std::vector<int> by_steps(n);
+    for (int k = 0; k < n; ++k) by_steps[k] = k;
+    std::stable_sort(by_steps.begin(), by_steps.end(), [&](int a, int b) { return ht[a].o.steps > ht[b].o.steps; });
+    for (int k : by_steps) {
+      ht[k].spill0 = nspill;
+      nspill += ht[k].spilln;
+    }
+  }
   SIMR_HIP(hipMemcpyAsync(g.tasks, ht, sizeof(LsmTask) * (size_t)n, hipMemcpyHostToDevice, s));
+  if (together) {
+    Prof pf(c, SIMR_PROF_SPILL, s);
+    SIMR_HIP(launch_spill_tasks(scheme, g.tasks, n, nspill, g.zero, g.zero_words, s));
+  }
   if (coop) {
     if (c->lsm_fail_test) SIMR_HIP(hipMemsetD32Async((hipDeviceptr_t)g.status, 1u, 1, s));
-    for (int k = 0; k < n; ++k) {
+    if (together) {
+      {
+        Prof pf(c, SIMR_PROF_GRAM, s);
+        SIMR_HIP(launch_gram_tasks(g.tasks, n, ngram, s));
+      }
+      Prof pf(c, SIMR_PROF_FACTOR, s);
+      SIMR_HIP(launch_factor_tasks(g.tasks, n, nfac, s));
+    }
+    for (int k = 0; k < n && !together; ++k) {
       Prof pf(c, SIMR_PROF_GRAM, s);
       SIMR_HIP(launch_lsm_gram(d[k], g.b[k].xs, g.b[k].vs, g.b[k].gram, s));
     }
-    for (int k = 0; k < n; ++k) {
+    for (int k = 0; k < n && !together; ++k) {
       Prof pf(c, SIMR_PROF_FACTOR, s);
       SIMR_HIP(launch_lsm_factor(d[k], opts[g.idx[k]].r * opts[g.idx[k]].T / opts[g.idx[k]].steps, g.b[k].gram,
                                  g.b[k].fac, g.b[k].st.flags, s));
@@ -1473,8 +1539,26 @@ size_t greeks_item_sums_offset(const GreeksItem& it) {
   return it.am ? (amer_pinned_bytes((int)it.count) + 63) / 64 * 64 : 0;
 }
 
+// The adjoint rows of every option of a group whose adjoints run in one launch (2 SIMR_NUM_GREEKS
+// doubles per block of the smallest adjoint block), then the sums of every option.
+struct GroupAdjoints {
+  std::vector<double*> gpart;
+  double* sums;  // kGreekSumsBytes per option
+};
+
+GroupAdjoints carve_group_adjoints(Carve& cv, const simr_option* opts, int64_t first, int64_t count) {
+  GroupAdjoints a;
+  for (int64_t k = 0; k < count; ++k) {
+    const int64_t nb = (opts[first + k].paths + kAdjMinBlock - 1) / kAdjMinBlock;
+    a.gpart.push_back(cv.take<double>((size_t)nb * 2 * SIMR_NUM_GREEKS));
+  }
+  a.sums = cv.take<double>(kGreekSumsBytes / sizeof(double) * (size_t)count);
+  return a;
+}
+
 // Workspace of an American group: the pass's buffers, then the adjoint's of its largest option
-// (the options' adjoints run one after another).
+// (used by the options' adjoints one after another) and, for adjoints in one launch, every option's
+// adjoint rows.
 size_t greeks_group_bytes(const simr_option* opts, int64_t first, int64_t count, int ck) {
   std::vector<int64_t> idx;
   int64_t P = 0;
@@ -1487,6 +1571,7 @@ size_t greeks_group_bytes(const simr_option* opts, int64_t first, int64_t count,
   Carve cv(nullptr);
   carve_amer_group(cv, opts, idx);
   carve_greeks_euro(cv, P, N, ck);
+  if (run_together(opts, idx)) carve_group_adjoints(cv, opts, first, count);
   return cv.off;
 }
 
@@ -1530,7 +1615,36 @@ simr_status greeks_enqueue_group(simr_ctx* ctx, const simr_option* opts, int sch
   Carve cv(d_ws);
   it->ag = carve_amer_group(cv, opts, idx);
   GreekBufs gb = carve_greeks_euro(cv, P, N, ck);
-  simr_status st = enqueue_american_group(ctx, scheme, opts, it->ag, false, stage, s, &it->coop);
+  simr_status st;
+  if (run_together(opts, idx)) {
+    const int n = (int)it->count;
+    const GroupAdjoints ga = carve_group_adjoints(cv, opts, it->first, n);
+    std::vector<int> ablock(n);
+    for (int k = 0; k < n; ++k) ablock[k] = adjoint_block(opts[it->first + k].paths, ck, ext, ctx->num_cus);
+    // one launch per run of consecutive options with the same block (the block fixes the rows)
+    struct Run { int first, count, grid; };
+    std::vector<Run> runs;
+    st = enqueue_american_group(ctx, scheme, opts, it->ag, false, stage, s, &it->coop, [&](int k, LsmTask* t) {
+      if (k == 0 || ablock[k] != ablock[k - 1]) runs.push_back(Run{k, 0, 0});
+      Run& r = runs.back();
+      t->gpart = ga.gpart[k];
+      t->adj0 = r.grid;
+      t->adjn = (int32_t)((opts[it->first + k].paths + ablock[k] - 1) / ablock[k]);
+      r.grid += t->adjn;
+      ++r.count;
+    });
+    if (st != SIMR_OK) return st;
+    for (const Run& r : runs) {
+      Prof pf(ctx, SIMR_PROF_ADJOINT, s);
+      SIMR_HIP(launch_adjoint_tasks(scheme, it->ag.tasks + r.first, r.count, r.grid, ck, ablock[r.first], s));
+    }
+    constexpr int stride = (int)(kGreekSumsBytes / sizeof(double));
+    SIMR_HIP(launch_sum_rows_tasks(it->ag.tasks, n, 2 * ng, stride, ga.sums + 2, s));
+    SIMR_HIP(hipMemcpyAsync(stage + greeks_item_sums_offset(*it), ga.sums, kGreekSumsBytes * (size_t)n,
+                            hipMemcpyDeviceToHost, s));
+    return SIMR_OK;
+  }
+  st = enqueue_american_group(ctx, scheme, opts, it->ag, false, stage, s, &it->coop);
   if (st != SIMR_OK) return st;
   for (int64_t k = 0; k < it->count; ++k) {
     const simr_option& o = opts[it->first + k];
@@ -2009,7 +2123,7 @@ simr_status basket_american_run(simr_ctx* c, int scheme, const simr_basket& b, c
   t.xchg = (unsigned long long*)(u.zero + 16);
   t.partials = u.partials;
   t.beta64 = want_beta ? u.beta64 : nullptr;
-  t.flags = (const int32_t*)(u.zero + 1);
+  t.flags = (int32_t*)(u.zero + 1);
   t.block0 = 0;
   t.nblocks = coop ? grids[0] : (int)((b.paths + kLsmBlock - 1) / kLsmBlock);
   simr_status st = basket_upload(c, scheme, b, u, &t, s);

@@ -78,27 +78,30 @@ __global__ __launch_bounds__(BLOCK) void batch_price_kernel(const DevOpt* __rest
 // row-major table of `ncol` doubles in a fixed order: thread t adds rows t, t + 256, ...
 // sequentially, then the 256 partial sums are combined by a fixed tree.  With opts == nullptr
 // a single set of rows [0, nrows) is summed, one block per column (the same order).
+__device__ __forceinline__ void sum_column(const double* __restrict__ rows, int32_t ncol, int32_t r0, int32_t nr,
+                                           int32_t c, double* __restrict__ out) {
+  __shared__ double s[256];
+  double acc = 0.0;
+  for (int32_t r = threadIdx.x; r < nr; r += 256) acc += rows[(size_t)(r0 + r) * ncol + c];
+  s[threadIdx.x] = acc;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *out = s[0];
+  __syncthreads();
+}
+
 __global__ __launch_bounds__(256) void finalize_rows_kernel(const double* __restrict__ rows, int32_t ncol,
                                                             const DevOpt* __restrict__ opts, int32_t nrows,
                                                             double* __restrict__ out) {
-  __shared__ double s[256];
   const int32_t r0 = opts ? opts[blockIdx.x].slot0 : 0;
   const int32_t nr = opts ? opts[blockIdx.x].ntiles : nrows;
   const int32_t c_begin = opts ? 0 : (int32_t)blockIdx.x;
   const int32_t c_end = opts ? ncol : (int32_t)blockIdx.x + 1;
   const size_t ob = opts ? (size_t)blockIdx.x * ncol : 0;
-  for (int32_t c = c_begin; c < c_end; ++c) {
-    double acc = 0.0;
-    for (int32_t r = threadIdx.x; r < nr; r += 256) acc += rows[(size_t)(r0 + r) * ncol + c];
-    s[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) out[ob + c] = s[0];
-    __syncthreads();
-  }
+  for (int32_t c = c_begin; c < c_end; ++c) sum_column(rows, ncol, r0, nr, c, out + ob + c);
 }
 
 // Copies a small host record (passed by value as the kernel argument) into device memory: the
@@ -129,14 +132,9 @@ __device__ __forceinline__ SIMR_GLOBAL char* uniform_row(float* row) {
   return (SIMR_GLOBAL char*)(uintptr_t)(((uint64_t)hi << 32) | lo);
 }
 
-template <int SCHEME, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void forward_spill_kernel(DevOpt o, float* __restrict__ xs,
-                                                              float* __restrict__ vs, uint32_t* __restrict__ zero,
-                                                              int64_t nzero) {
-  const uint32_t p = blockIdx.x * BLOCK + threadIdx.x;
-  // the words the later kernels of this option expect at zero (flags, exchange) are cleared here
-  for (int64_t i = p; i < nzero; i += (int64_t)gridDim.x * BLOCK) zero[i] = 0u;
-  if (p >= (uint32_t)o.paths) return;
+template <int SCHEME>
+__device__ __forceinline__ void spill_path(const DevOpt& o, uint32_t p, float* __restrict__ xs,
+                                           float* __restrict__ vs) {
   const size_t P = (size_t)o.paths;
   // each store at the row's uniform base plus the lane's 32-bit byte offset (paths <= 2^30):
   // the scalar-base form, with no 64-bit address arithmetic per store in the step loop
@@ -153,6 +151,49 @@ __global__ __launch_bounds__(BLOCK) void forward_spill_kernel(DevOpt o, float* _
     *(SIMR_GLOBAL float*)(xr + boff) = x;
     *(SIMR_GLOBAL float*)(vr + boff) = v;
   }
+}
+
+template <int SCHEME, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void forward_spill_kernel(DevOpt o, float* __restrict__ xs,
+                                                              float* __restrict__ vs, uint32_t* __restrict__ zero,
+                                                              int64_t nzero) {
+  const uint32_t p = blockIdx.x * BLOCK + threadIdx.x;
+  // the words the later kernels of this option expect at zero (flags, exchange) are cleared here
+  for (int64_t i = p; i < nzero; i += (int64_t)gridDim.x * BLOCK) zero[i] = 0u;
+  if (p >= (uint32_t)o.paths) return;
+  spill_path<SCHEME>(o, p, xs, vs);
+}
+
+// The task of a batched launch that block u belongs to: the one with first <= u < first + count in
+// the two named fields.  Each lane looks at one task, so 64 tasks cost one memory round trip (a
+// binary search would cost one per level); every block belongs to exactly one task.
+template <int32_t LsmTask::*FIRST, int32_t LsmTask::*COUNT>
+__device__ __forceinline__ int32_t task_of_block(const LsmTask* __restrict__ tasks, int32_t ntasks, uint32_t u) {
+  const int32_t lane = (int32_t)(threadIdx.x & (kWave - 1));
+  for (int32_t base = 0; base < ntasks; base += kWave) {
+    const int32_t t = base + lane;
+    const bool mine = t < ntasks && u - (uint32_t)(tasks[t].*FIRST) < (uint32_t)(tasks[t].*COUNT);
+    const uint64_t m = __ballot(mine);
+    if (m) return __builtin_amdgcn_readfirstlane(base + __builtin_ctzll(m));
+  }
+  return -1;
+}
+
+// The spills of several options in one launch, longest first (spill0 in descending steps).  One
+// option of the paper's 25,000 paths is 391 waves on 1024 SIMDs and as long as its serial steps,
+// so 30 such launches in a row left most of the chip idle: bound by the latency of one path's
+// step chain, not by issue.
+template <int SCHEME, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void spill_tasks_kernel(const LsmTask* __restrict__ tasks, int32_t ntasks,
+                                                            uint32_t* __restrict__ zero, int64_t nzero) {
+  for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < nzero; i += (int64_t)gridDim.x * BLOCK) zero[i] = 0u;
+  const int32_t t = task_of_block<&LsmTask::spill0, &LsmTask::spilln>(tasks, ntasks, blockIdx.x);
+  if (t < 0) return;
+  const LsmTask& T = tasks[t];
+  const DevOpt o = T.o;  // a copy: its fields then stay in scalar registers across the stores
+  const uint32_t p = (blockIdx.x - (uint32_t)T.spill0) * BLOCK + threadIdx.x;
+  if (p >= (uint32_t)o.paths) return;
+  spill_path<SCHEME>(o, p, T.xs, T.vs);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -415,7 +456,7 @@ __host__ __device__ constexpr int gram_moment(int p, int q) { return (p + q) * (
 constexpr int kBasisE[6] = {0, 1, 2, 0, 1, 0};
 constexpr int kBasisF[6] = {0, 0, 0, 1, 1, 2};
 
-// Block (date n = blockIdx.x + 1, chunk blockIdx.y): FP32 sums per lane over the chunk's paths
+// Block (date n, chunk): FP32 sums per lane over the chunk's paths
 // p = chunk * (BLOCK * per_lane) + k * BLOCK + lane, FP32 block sums, one row per (date, chunk).
 // With 6 functions the sums are the 15 moments (the 21 Gram entries hold only 15 distinct
 // monomials: 3 products and 14 accumulations per path instead of 20); with 10 the Gram's upper
@@ -428,18 +469,17 @@ constexpr int kBasisF[6] = {0, 0, 0, 1, 1, 2};
 constexpr int kGramMaxPerLane = 16;
 
 template <int BLOCK, int NB>
-__global__ __launch_bounds__(BLOCK) void lsm_gram_kernel(DevOpt o, const float* __restrict__ xs,
-                                                         const float* __restrict__ vs, int32_t per_lane,
-                                                         float* __restrict__ gram) {
+__device__ __forceinline__ void gram_block(const DevOpt& o, int32_t n, uint32_t chunk, uint32_t chunks,
+                                           const float* __restrict__ xs, const float* __restrict__ vs,
+                                           int32_t per_lane, float* __restrict__ gram) {
   constexpr int kGramSums = LsmLayout<NB>::kSums;
   constexpr int kGramRow = LsmLayout<NB>::kRow;
   __shared__ float s_red[kGramSums * (BLOCK / kWave)];
-  const int n = blockIdx.x + 1;
   const size_t P = (size_t)o.paths;
   float acc[kGramSums];
 #pragma unroll
   for (int i = 0; i < kGramSums; ++i) acc[i] = 0.0f;
-  const uint32_t p0 = blockIdx.y * (uint32_t)(BLOCK * per_lane) + threadIdx.x;
+  const uint32_t p0 = chunk * (uint32_t)(BLOCK * per_lane) + threadIdx.x;
   const uint32_t plast = (uint32_t)o.paths - 1;
   const SIMR_GLOBAL float* __restrict__ xr = as_global(xs) + (size_t)(n - 1) * P;
   const SIMR_GLOBAL float* __restrict__ vr = as_global(vs) + (size_t)(n - 1) * P;
@@ -493,10 +533,31 @@ __global__ __launch_bounds__(BLOCK) void lsm_gram_kernel(DevOpt o, const float* 
   if constexpr (NB != 6) acc[0] = acc[kGramSums - 1];
   block_sum<BLOCK, kGramSums, float>(acc, s_red);
   if (threadIdx.x == 0) {
-    float* row = gram + ((size_t)n * gridDim.y + blockIdx.y) * kGramRow;
+    float* row = gram + ((size_t)n * chunks + chunk) * kGramRow;
 #pragma unroll
     for (int i = 0; i < kGramSums; ++i) row[i] = acc[i];
   }
+}
+
+template <int BLOCK, int NB>
+__global__ __launch_bounds__(BLOCK) void lsm_gram_kernel(DevOpt o, const float* __restrict__ xs,
+                                                         const float* __restrict__ vs, int32_t per_lane,
+                                                         float* __restrict__ gram) {
+  gram_block<BLOCK, NB>(o, (int32_t)blockIdx.x + 1, blockIdx.y, gridDim.y, xs, vs, per_lane, gram);
+}
+
+// The Gram sums of several options in one launch (dates fastest, as in the launch of one).  Held to
+// 8 waves per SIMD: one register more than the launch of one option's 64 would cost a wave.
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK, 8) void gram_tasks_kernel(const LsmTask* __restrict__ tasks, int32_t ntasks) {
+  const int32_t t = task_of_block<&LsmTask::gram0, &LsmTask::gramn>(tasks, ntasks, blockIdx.x);
+  if (t < 0) return;
+  const LsmTask& T = tasks[t];
+  const DevOpt o = T.o;
+  const uint32_t u = blockIdx.x - (uint32_t)T.gram0, dates = (uint32_t)o.steps - 1;
+  const uint32_t chunk = u / dates;
+  gram_block<BLOCK, 6>(o, (int32_t)(u - chunk * dates) + 1, chunk, (uint32_t)T.chunks, T.xs, T.vs, T.per_lane,
+                       T.gram);
 }
 
 __device__ __forceinline__ double readlane_d(double x, int l) {
@@ -506,7 +567,7 @@ __device__ __forceinline__ double readlane_d(double x, int l) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// One block per date n = blockIdx.x + 1.  The chunk rows are summed in FP64 in a fixed order:
+// One block per date n.  The chunk rows are summed in FP64 in a fixed order:
 // thread t adds rows t, t + 256, ... (each row read at once in 16-byte loads, so a date's rows
 // arrive in one memory round trip instead of one per 8 chunks), each wave sums its lanes by a
 // fixed butterfly, and lane e of wave 0 adds the four waves' partials of entry e in wave order.
@@ -519,14 +580,11 @@ __device__ __forceinline__ double readlane_d(double x, int l) {
 // columns, M = P^T (L L^T)^{-1} P (36), rank, count, valid.
 constexpr int kFactorThreads = 256;
 
-__global__ __launch_bounds__(kFactorThreads) void lsm_factor_kernel(int32_t chunks, double rdt,
-                                                                    const float* __restrict__ gram,
-                                                                    double* __restrict__ fac,
-                                                                    int32_t* __restrict__ flags) {
+__device__ __forceinline__ void factor_block(int32_t n, int32_t chunks, double rdt, const float* __restrict__ gram,
+                                             double* __restrict__ fac, int32_t* __restrict__ flags) {
   constexpr int W = kFactorThreads / kWave;
   static_assert(kGramRow % 4 == 0 && kGramSums <= kGramRow, "rows of whole 16-byte words");
   __shared__ double s_part[kGramSums * W];
-  const int n = blockIdx.x + 1;
   const int lane = threadIdx.x & (kWave - 1);
   const int wid = threadIdx.x / kWave;
   double part[kGramSums];
@@ -662,6 +720,22 @@ __global__ __launch_bounds__(kFactorThreads) void lsm_factor_kernel(int32_t chun
     rec[51] = exp(rdt * (double)n);
     if (rank < 6) atomicOr(flags, 2);
   }
+}
+
+__global__ __launch_bounds__(kFactorThreads) void lsm_factor_kernel(int32_t chunks, double rdt,
+                                                                    const float* __restrict__ gram,
+                                                                    double* __restrict__ fac,
+                                                                    int32_t* __restrict__ flags) {
+  factor_block((int32_t)blockIdx.x + 1, chunks, rdt, gram, fac, flags);
+}
+
+// The factorisations of every date of several options in one launch.
+__global__ __launch_bounds__(kFactorThreads) void factor_tasks_kernel(const LsmTask* __restrict__ tasks,
+                                                                      int32_t ntasks) {
+  const int32_t t = task_of_block<&LsmTask::fac0, &LsmTask::facn>(tasks, ntasks, blockIdx.x);
+  if (t < 0) return;
+  const LsmTask& T = tasks[t];
+  factor_block((int32_t)(blockIdx.x - (uint32_t)T.fac0) + 1, T.chunks, T.rdt, T.gram, T.fac, T.flags);
 }
 
 // The same record for a basis of NB functions (NB = 10): the lanes sum the chunk rows as above,
@@ -957,9 +1031,9 @@ __global__ __launch_bounds__(BLOCK) void lsm_persistent_kernel(
   }
   const LsmTask& T = tasks[t];
   const DevOpt o = T.o;
-  const SIMR_GLOBAL float* __restrict__ xs = as_global(T.xs);
-  const SIMR_GLOBAL float* __restrict__ vs = as_global(T.vs);
-  const SIMR_GLOBAL double* __restrict__ fac = as_global(T.fac);
+  const SIMR_GLOBAL float* __restrict__ xs = as_global((const float*)T.xs);
+  const SIMR_GLOBAL float* __restrict__ vs = as_global((const float*)T.vs);
+  const SIMR_GLOBAL double* __restrict__ fac = as_global((const double*)T.fac);
   const uint32_t G = (uint32_t)T.nblocks;
   const uint32_t blk = blockIdx.x - (uint32_t)T.block0;
   const uint32_t npoll = (G + kRowsPerPoller - 1) / kRowsPerPoller;  // waves 0 .. npoll - 1 poll
@@ -1626,10 +1700,9 @@ __device__ __forceinline__ float fte_reverse(const DevOpt& o, float v, float z1,
 // for American options, whose stopping decisions would be re-weighted onto other paths).
 // gpartials: 2 NG doubles per block (sums, then sums of squares), NG = 7 or 9.
 template <int BLOCK, int CK, bool EXT, int SCHEME>
-__global__ __launch_bounds__(BLOCK) void adjoint_kernel(DevOpt o, const float* __restrict__ ck_base,
-                                                        size_t ck_stride, const float* __restrict__ xstop,
-                                                        const int32_t* __restrict__ tau,
-                                                        double* __restrict__ gpartials) {
+__device__ __forceinline__ void adjoint_sweep(const DevOpt& o, uint32_t blk, const float* __restrict__ ck_base,
+                                              size_t ck_stride, const float* __restrict__ xstop,
+                                              const int32_t* __restrict__ tau, double* __restrict__ gpartials) {
   constexpr int W = BLOCK / kWave;
   constexpr int NG = EXT ? 9 : 7;
   __shared__ double s_red[2 * NG * W];
@@ -1642,7 +1715,7 @@ __global__ __launch_bounds__(BLOCK) void adjoint_kernel(DevOpt o, const float* _
   const size_t P = (size_t)o.paths;
   const int ncls = min((o.steps + 7) / 8, kAdjClasses);
   {
-    const uint32_t p = blockIdx.x * BLOCK + threadIdx.x;
+    const uint32_t p = blk * BLOCK + threadIdx.x;
     int32_t ts = 0;  // 0: nothing to sweep
     float xs = 0.0f;
     int c = ncls;
@@ -1694,7 +1767,7 @@ __global__ __launch_bounds__(BLOCK) void adjoint_kernel(DevOpt o, const float* _
     __syncthreads();
   }
   const int src = s_slot[threadIdx.x];
-  const uint32_t p = blockIdx.x * BLOCK + (uint32_t)src;
+  const uint32_t p = blk * BLOCK + (uint32_t)src;
   const int32_t ts = s_ts[src];
   float g[NG];
 #pragma unroll
@@ -1800,8 +1873,35 @@ __global__ __launch_bounds__(BLOCK) void adjoint_kernel(DevOpt o, const float* _
   block_sum<BLOCK, 2 * NG, double>(vals, s_red);
   if (threadIdx.x == 0) {
 #pragma unroll
-    for (int i = 0; i < 2 * NG; ++i) gpartials[(size_t)blockIdx.x * 2 * NG + i] = vals[i];
+    for (int i = 0; i < 2 * NG; ++i) gpartials[(size_t)blk * 2 * NG + i] = vals[i];
   }
+}
+
+template <int BLOCK, int CK, bool EXT, int SCHEME>
+__global__ __launch_bounds__(BLOCK) void adjoint_kernel(DevOpt o, const float* __restrict__ ck_base,
+                                                        size_t ck_stride, const float* __restrict__ xstop,
+                                                        const int32_t* __restrict__ tau,
+                                                        double* __restrict__ gpartials) {
+  adjoint_sweep<BLOCK, CK, EXT, SCHEME>(o, blockIdx.x, ck_base, ck_stride, xstop, tau, gpartials);
+}
+
+// The adjoints of several American options in one launch, each block working on one task.
+template <int BLOCK, int CK, int SCHEME>
+__global__ __launch_bounds__(BLOCK) void adjoint_tasks_kernel(const LsmTask* __restrict__ tasks, int32_t ntasks) {
+  const int32_t t = task_of_block<&LsmTask::adj0, &LsmTask::adjn>(tasks, ntasks, blockIdx.x);
+  if (t < 0) return;
+  const LsmTask& T = tasks[t];
+  const DevOpt o = T.o;
+  const size_t P = (size_t)o.paths;
+  adjoint_sweep<BLOCK, CK, false, SCHEME>(o, blockIdx.x - (uint32_t)T.adj0, T.vs + (size_t)(CK - 1) * P,
+                                          (size_t)CK * P, T.xs, T.tau, T.gpart);
+}
+
+// Column blockIdx.x of task blockIdx.y's adjoint rows summed as finalize_rows_kernel sums them.
+__global__ __launch_bounds__(256) void sum_rows_tasks_kernel(const LsmTask* __restrict__ tasks, int32_t ncol,
+                                                             int32_t out_stride, double* __restrict__ out) {
+  const LsmTask& T = tasks[blockIdx.y];
+  sum_column(T.gpart, ncol, 0, T.adjn, (int32_t)blockIdx.x, out + (size_t)blockIdx.y * out_stride + blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1926,6 +2026,30 @@ hipError_t launch_forward_spill(int scheme, const DevOpt& o, float* xs, float* v
   return hipGetLastError();
 }
 
+hipError_t launch_spill_tasks(int scheme, const LsmTask* tasks, int ntasks, int grid, uint32_t* zero, int64_t nzero,
+                              hipStream_t s) {
+#define SIMR_SPILL(S)                                                                                            \
+  if (scheme == S)                                                                                               \
+    hipLaunchKernelGGL((spill_tasks_kernel<S, kLsmBlock>), dim3(grid), dim3(kLsmBlock), 0, s, tasks, ntasks, zero, \
+                       nzero);
+  SIMR_SPILL(0) SIMR_SPILL(1) SIMR_SPILL(2) SIMR_SPILL(3) SIMR_SPILL(4)
+#undef SIMR_SPILL
+  if (scheme < 0 || scheme > 4) return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_gram_tasks(const LsmTask* tasks, int ntasks, int grid, hipStream_t s) {
+  if (grid < 1) return hipSuccess;  // every option has one step: no dates
+  hipLaunchKernelGGL(gram_tasks_kernel<kLsmBlock>, dim3(grid), dim3(kLsmBlock), 0, s, tasks, ntasks);
+  return hipGetLastError();
+}
+
+hipError_t launch_factor_tasks(const LsmTask* tasks, int ntasks, int grid, hipStream_t s) {
+  if (grid < 1) return hipSuccess;
+  hipLaunchKernelGGL(factor_tasks_kernel, dim3(grid), dim3(kFactorThreads), 0, s, tasks, ntasks);
+  return hipGetLastError();
+}
+
 hipError_t launch_lsm(const DevOpt& o, const float* xs, const float* vs, float* hcash, int32_t* tau,
                       const LsmState& st, double* partials, hipStream_t s) {
   const int grid = (o.paths + kLsmBlock - 1) / kLsmBlock;
@@ -2030,7 +2154,7 @@ std::vector<LsmLaunchSet> lsm_coop_plan(const std::vector<int64_t>& paths, int n
 hipError_t launch_lsm_gram(const DevOpt& o, const float* xs, const float* vs, float* gram, hipStream_t s, int nb) {
   if (o.steps < 2) return hipSuccess;
   const int chunks = lsm_gram_chunks(o.paths);
-  const int per_lane = (int)((o.paths + (int64_t)chunks * kLsmBlock - 1) / ((int64_t)chunks * kLsmBlock));
+  const int per_lane = lsm_gram_per_lane(o.paths);
   if (per_lane > kGramMaxPerLane) return hipErrorInvalidValue;  // the chunks are sized to keep it <= 16
   if (nb == 6) {
     hipLaunchKernelGGL((lsm_gram_kernel<kLsmBlock, 6>), dim3(o.steps - 1, chunks), dim3(kLsmBlock), 0, s, o, xs,
@@ -2164,6 +2288,35 @@ hipError_t launch_adjoint(int scheme, const DevOpt& o, int ck, int block, bool e
   if (scheme == 2) return launch_adjoint_s<2>(o, ck, block, ext, ck_base, ck_stride, xstop, tau, gpart, s);
   if (scheme == 3) return launch_adjoint_s<3>(o, ck, block, ext, ck_base, ck_stride, xstop, tau, gpart, s);
   return hipErrorInvalidValue;
+}
+
+template <int SCHEME>
+static hipError_t launch_adjoint_tasks_s(const LsmTask* tasks, int ntasks, int grid, int ck, int block,
+                                         hipStream_t s) {
+#define SIMR_ADJ(B, C)                                                                                       \
+  if (block == B && ck == C) {                                                                               \
+    hipLaunchKernelGGL((adjoint_tasks_kernel<B, C, SCHEME>), dim3(grid), dim3(B), 0, s, tasks, ntasks);      \
+    return hipGetLastError();                                                                                \
+  }
+  SIMR_ADJ(1024, 8) SIMR_ADJ(1024, 16) SIMR_ADJ(512, 8) SIMR_ADJ(512, 16) SIMR_ADJ(512, 32)
+  SIMR_ADJ(256, 8) SIMR_ADJ(256, 16) SIMR_ADJ(256, 32)
+#undef SIMR_ADJ
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_adjoint_tasks(int scheme, const LsmTask* tasks, int ntasks, int grid, int ck, int block,
+                                hipStream_t s) {
+  if (scheme == 0) return launch_adjoint_tasks_s<0>(tasks, ntasks, grid, ck, block, s);
+  if (scheme == 1) return launch_adjoint_tasks_s<1>(tasks, ntasks, grid, ck, block, s);
+  if (scheme == 2) return launch_adjoint_tasks_s<2>(tasks, ntasks, grid, ck, block, s);
+  if (scheme == 3) return launch_adjoint_tasks_s<3>(tasks, ntasks, grid, ck, block, s);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_sum_rows_tasks(const LsmTask* tasks, int ntasks, int ncol, int out_stride, double* out,
+                                 hipStream_t s) {
+  hipLaunchKernelGGL(sum_rows_tasks_kernel, dim3(ncol, ntasks), dim3(256), 0, s, tasks, ncol, out_stride, out);
+  return hipGetLastError();
 }
 
 hipError_t launch_debug_draws(uint64_t seed, uint32_t stream, int64_t path0, int64_t npaths, int32_t step0,

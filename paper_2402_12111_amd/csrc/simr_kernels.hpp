@@ -48,20 +48,34 @@ struct LsmState {
 // nblocks) of the launch work on it and exchange only among themselves.
 struct LsmTask {
   DevOpt o;
-  const float* xs;           // spilled states, row n - 1 = date n, P floats per row
-  const float* vs;
-  const double* fac;         // factor record of every date
+  float* xs;                 // spilled states, row n - 1 = date n, P floats per row
+  float* vs;
+  double* fac;               // factor record of every date
   int32_t* tau;              // out: exercise index per path
   unsigned long long* xchg;  // [2][nblocks][8] tagged words of the blocks' sums; zero before the launch
   double* partials;          // out: {sum X, sum X^2} per block of the task
   double* beta64;            // out, may be null: the 6 FP64 coefficients per date (first block)
-  const int32_t* flags;      // SIMR_LSM_FEW_ITM | SIMR_LSM_DROPPED of the option (read by the finish)
+  int32_t* flags;            // SIMR_LSM_FEW_ITM | SIMR_LSM_DROPPED of the option (read by the finish)
   int32_t block0, nblocks;
+  // the batched launches over all tasks of a pass (spill, Gram pre-pass, factors, adjoints):
+  // task t's blocks [first, first + count) of each
+  float* gram;               // Gram sums of every (date, chunk)
+  double* gpart;             // adjoint rows
+  double rdt;                // r T / N
+  int32_t spill0, spilln;
+  int32_t gram0, gramn;
+  int32_t fac0, facn;
+  int32_t adj0, adjn;
+  int32_t chunks, per_lane;  // of the Gram pre-pass
 };
 
 // Chunks of paths per date of the Gram pre-pass: each lane sums at most 16 paths in FP32.
 inline int lsm_gram_chunks(int64_t paths) {
   return (int)((paths + (int64_t)kLsmBlock * 16 - 1) / ((int64_t)kLsmBlock * 16));
+}
+inline int lsm_gram_per_lane(int64_t paths) {
+  const int64_t lanes = (int64_t)lsm_gram_chunks(paths) * kLsmBlock;
+  return (int)((paths + lanes - 1) / lanes);
 }
 constexpr int kLsmGramRow = 16;  // floats per (date, chunk) row of Gram sums (15 moments)
 constexpr int kLsmFacRec = 64;   // doubles per date of factor record
@@ -90,6 +104,12 @@ hipError_t launch_lsm_gram(const DevOpt& o, const float* xs, const float* vs, fl
                            int nb = 6);
 hipError_t launch_lsm_factor(const DevOpt& o, double rdt, const float* gram, double* fac, int32_t* flags,
                              hipStream_t s, int nb = 6);
+// The same three passes for every task of a device table in one launch each (grid: the sum of
+// the tasks' spilln, gramn or facn); the spill also zeroes zero[0, nzero).
+hipError_t launch_spill_tasks(int scheme, const LsmTask* tasks, int ntasks, int grid, uint32_t* zero, int64_t nzero,
+                              hipStream_t s);
+hipError_t launch_gram_tasks(const LsmTask* tasks, int ntasks, int grid, hipStream_t s);
+hipError_t launch_factor_tasks(const LsmTask* tasks, int ntasks, int grid, hipStream_t s);
 // tasks: device array, sorted by block0, block0 relative to this launch.
 hipError_t launch_lsm_coop(const LsmTask* tasks, int ntasks, int block, int ppl, int grid, int32_t* status,
                            hipStream_t s, int nb = 6);
@@ -123,6 +143,13 @@ hipError_t launch_forward_ckpt(int scheme, const DevOpt& o, int ck, float* ckbuf
 // gpart: 14 (ext: 18) doubles per block of `block` paths (adjoint_block).
 hipError_t launch_adjoint(int scheme, const DevOpt& o, int ck, int block, bool ext, const float* ck_base,
                           size_t ck_stride, const float* xstop, const int32_t* tau, double* gpart, hipStream_t s);
+// The adjoints of `ntasks` American options of a device table in one launch (grid: the sum of their
+// adjn, all of `block` threads), their rows into each task's gpart; then (launch_sum_rows_tasks)
+// the column sums of every task's rows: out[t out_stride + c], c < ncol.
+hipError_t launch_adjoint_tasks(int scheme, const LsmTask* tasks, int ntasks, int grid, int ck, int block,
+                                hipStream_t s);
+hipError_t launch_sum_rows_tasks(const LsmTask* tasks, int ntasks, int ncol, int out_stride, double* out,
+                                 hipStream_t s);
 hipError_t launch_debug_draws(uint64_t seed, uint32_t stream, int64_t path0, int64_t npaths, int32_t step0,
                               int32_t nsteps, uint32_t* words, float* unif, float* norm, hipStream_t s);
 hipError_t launch_debug_paths(int scheme, const DevOpt& o, float* xT, float* vT, float* pay, hipStream_t s);
