@@ -250,11 +250,12 @@ __device__ __forceinline__ float tg_variance(const DevOpt& o, float v, float z1)
   return fmaxf(m * __builtin_fmaf(fs, z1, fm), 0.0f);
 }
 
-// Broadie and Kaya's exact step (FP64; the FP32 state widened and rounded back).
+// Broadie and Kaya's exact step (FP64; the FP32 state widened and rounded back).  The lanes of a
+// wave share the work of its 64 paths, so every lane has to be active.
 __device__ __noinline__ void bk_transition(const DevOpt& o, float& x, float& v, const Draw& d) {
   const double vu = (double)v;
   const double vt = bk::variance(vu, o.bk_kappa, o.bk_theta, o.bk_xi, o.bk_dt, (double)d.u);
-  const double iv = bk::integrated_variance(vu, vt, o.bk_kappa, o.bk_theta, o.bk_xi, o.bk_dt, (double)d.u2);
+  const double iv = bk::integrated_variance<bk::WaveLanes>(vu, vt, o.bk_kappa, o.bk_theta, o.bk_xi, o.bk_dt, (double)d.u2);
   const bool noisy = o.bk_xi > 0.0;
   const double wv = noisy ? (vt - vu - o.bk_kappa * o.bk_theta * o.bk_dt + o.bk_kappa * iv) / o.bk_xi : 0.0;
   const double rh = noisy ? o.bk_rho : 0.0;

@@ -132,6 +132,13 @@ __device__ __forceinline__ SIMR_GLOBAL char* uniform_row(float* row) {
   return (SIMR_GLOBAL char*)(uintptr_t)(((uint64_t)hi << 32) | lo);
 }
 
+// Whether a lane with path p leaves now: past the last path, except that the Broadie-Kaya step needs
+// whole waves, so there a wave leaves only if all its paths are past the last.
+template <int SCHEME>
+__device__ __forceinline__ bool past_end(uint32_t p, int32_t paths) {
+  return (SCHEME == 4 ? (p & ~(uint32_t)(kWave - 1)) : p) >= (uint32_t)paths;
+}
+
 template <int SCHEME>
 __device__ __forceinline__ void spill_path(const DevOpt& o, uint32_t p, float* __restrict__ xs,
                                            float* __restrict__ vs) {
@@ -148,6 +155,7 @@ __device__ __forceinline__ void spill_path(const DevOpt& o, uint32_t p, float* _
     SIMR_GLOBAL char* xr = uniform_row(xs + (size_t)n * P);
     SIMR_GLOBAL char* vr = uniform_row(vs + (size_t)n * P);
     asm volatile("" : "+v"(boff));  // a 32-bit value of this step, not a hoisted 64-bit one
+    if (SCHEME == 4 && p >= (uint32_t)P) continue;
     *(SIMR_GLOBAL float*)(xr + boff) = x;
     *(SIMR_GLOBAL float*)(vr + boff) = v;
   }
@@ -160,7 +168,7 @@ __global__ __launch_bounds__(BLOCK) void forward_spill_kernel(DevOpt o, float* _
   const uint32_t p = blockIdx.x * BLOCK + threadIdx.x;
   // the words the later kernels of this option expect at zero (flags, exchange) are cleared here
   for (int64_t i = p; i < nzero; i += (int64_t)gridDim.x * BLOCK) zero[i] = 0u;
-  if (p >= (uint32_t)o.paths) return;
+  if (past_end<SCHEME>(p, o.paths)) return;
   spill_path<SCHEME>(o, p, xs, vs);
 }
 
@@ -192,7 +200,7 @@ __global__ __launch_bounds__(BLOCK) void spill_tasks_kernel(const LsmTask* __res
   const LsmTask& T = tasks[t];
   const DevOpt o = T.o;  // a copy: its fields then stay in scalar registers across the stores
   const uint32_t p = (blockIdx.x - (uint32_t)T.spill0) * BLOCK + threadIdx.x;
-  if (p >= (uint32_t)o.paths) return;
+  if (past_end<SCHEME>(p, o.paths)) return;
   spill_path<SCHEME>(o, p, T.xs, T.vs);
 }
 
@@ -1939,12 +1947,13 @@ template <int SCHEME>
 __global__ __launch_bounds__(256) void debug_paths_kernel(DevOpt o, float* __restrict__ xT, float* __restrict__ vT,
                                                           float* __restrict__ pay) {
   const uint32_t p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= (uint32_t)o.paths) return;
+  if (past_end<SCHEME>(p, o.paths)) return;
   float x = 0.0f, v = o.v0;
   for (int32_t n = 0; n < o.steps; ++n) {
     const Draw d = draw(o, (uint32_t)n, p);
     transition<SCHEME>(o, x, v, d);
   }
+  if (p >= (uint32_t)o.paths) return;
   if (xT) xT[p] = x;
   if (vT) vT[p] = v;
   if (pay) pay[p] = o.disc * intrinsic(o, asset(o, x));
