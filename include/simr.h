@@ -451,9 +451,10 @@ simr_status simr_debug_basket_lsm(simr_ctx* ctx, const simr_basket* b, const sim
  * induction then gives up at once, the launch completes, and the call returns SIMR_ENUMERIC
  * ("Longstaff-Schwartz exchange wait timed out").  The next call in mode 0 runs normally.
  * modes 3 and 4: as mode 0, with every cooperative launch of single-asset options on 256-thread
- * blocks (four times the paths per lane) or on 1024-thread blocks; mode 0 takes per launch the
- * size that holds more options co-resident (two options of 2^20 paths fit one launch only on
- * 256-thread blocks).  An option's paths per block, not the block size, fix its summation
+ * blocks (four times the paths per lane), or every one on 1024-thread blocks; mode 0 takes per launch the
+ * layout that holds more options co-resident (two options of 2^20 paths fit one launch only on
+ * 256-thread blocks; options of up to 64 blocks take blocks with a wave of their own for the
+ * exchange).  An option's paths per block, not the layout, fix its summation
  * order, so modes 0, 3 and 4 give the same bits. */
 simr_status simr_set_lsm_launch(simr_ctx* ctx, int32_t mode, int32_t grid_max);
 

@@ -164,6 +164,7 @@ struct simr_ctx {
   double prof_ms[SIMR_PROF_GROUPS] = {};
   int64_t prof_n[SIMR_PROF_GROUPS] = {};
   int num_cus = 0;
+  CoopCaps coop_caps{};        // blocks per CU of the induction's layouts, queried by simr_create
   std::string arch;
   int lsm_grid_max = 64;       // largest cooperative grid of the backward induction
   int lsm_block = 0;           // its block size: 0 chosen per launch, or fixed at 1024 or 256
@@ -927,10 +928,10 @@ simr_status enqueue_american_group(simr_ctx* c, int scheme, const simr_option* o
     if (st != SIMR_OK) return st;
     paths[k] = opts[g.idx[k]].paths;
   }
-  std::vector<int> grids;
+  std::vector<LsmPlace> at(n, LsmPlace{0, 0, -1});
   std::vector<LsmLaunchSet> sets;
   auto plan = [&]() {
-    if (!c->lsm_per_date) sets = lsm_coop_plan(paths, c->num_cus, c->lsm_grid_max, &grids, 6, c->lsm_block);
+    if (!c->lsm_per_date) sets = lsm_coop_plan(c->coop_caps, paths, c->num_cus, c->lsm_grid_max, &at, 6, c->lsm_block);
   };
   bool together = run_together(opts, g.idx);
   if (together) {
@@ -950,14 +951,6 @@ simr_status enqueue_american_group(simr_ctx* c, int scheme, const simr_option* o
   const bool coop = !sets.empty();
   // the task table: the cooperative launches' blocks, and the finish's partial rows
   LsmTask* ht = (LsmTask*)stage;
-  std::vector<int> block0(n, 0);
-  for (const LsmLaunchSet& ls : sets) {
-    int b0 = 0;
-    for (int k = ls.first; k < ls.first + ls.count; ++k) {
-      block0[k] = b0;
-      b0 += grids[k];
-    }
-  }
   int32_t ngram = 0, nfac = 0;
   for (int k = 0; k < n; ++k) {
     const LsmBufs& b = g.b[k];
@@ -973,8 +966,9 @@ simr_status enqueue_american_group(simr_ctx* c, int scheme, const simr_option* o
     t.partials = b.partials;
     t.beta64 = want_beta ? b.st.beta64 : nullptr;
     t.flags = b.st.flags;
-    t.block0 = block0[k];
-    t.nblocks = coop ? grids[k] : b.nblk;
+    t.block0 = at[k].block0;
+    t.nblocks = coop ? at[k].nblocks : b.nblk;
+    t.xcd = at[k].xcd;
     t.gram = b.gram;
     t.rdt = o.r * o.T / o.steps;
     t.chunks = lsm_gram_chunks(o.paths);
@@ -1025,7 +1019,7 @@ simr_status enqueue_american_group(simr_ctx* c, int scheme, const simr_option* o
     }
     for (const LsmLaunchSet& ls : sets) {
       Prof pf(c, SIMR_PROF_LSM, s);
-      SIMR_HIP(launch_lsm_coop(g.tasks + ls.first, ls.count, ls.block, ls.ppl, ls.grid, g.status, s));
+      SIMR_HIP(launch_lsm_coop(g.tasks + ls.first, ls.count, ls, g.status, s));
     }
   } else {
     Prof pf(c, SIMR_PROF_LSM, s);
@@ -1138,6 +1132,7 @@ simr_status simr_create(simr_ctx** ctx, int device) {
   simr_status st;
   {
     DeviceGuard g(device);
+    c->coop_caps = lsm_coop_caps();
     st = build_tg_table(c);
     if (st == SIMR_OK) {
       void* ptr = nullptr;
@@ -1587,8 +1582,8 @@ std::vector<GreeksItem> greeks_plan(simr_ctx* ctx, const simr_option* opts, int6
       // launch holds at most 1024 blocks, so at most 1024 options), as many as fit the workspace
       std::vector<int64_t> paths;
       for (int64_t k = i; k < n && k < i + 1024 && american(opts[k]); ++k) paths.push_back(opts[k].paths);
-      std::vector<int> grids;
-      const std::vector<LsmLaunchSet> sets = lsm_coop_plan(paths, ctx->num_cus, ctx->lsm_grid_max, &grids, 6,
+      std::vector<LsmPlace> at;
+      const std::vector<LsmLaunchSet> sets = lsm_coop_plan(ctx->coop_caps, paths, ctx->num_cus, ctx->lsm_grid_max, &at, 6,
                                                            ctx->lsm_block);
       it.count = sets.empty() ? 1 : sets[0].count;
       while (it.count > 1 && greeks_group_bytes(opts, i, it.count, ck) > ws_bytes) --it.count;
@@ -2109,9 +2104,10 @@ double basket_intrinsic(const simr_basket& b, double B) {
 // induction on the 10-function basis, then the finish; synchronises the stream.
 simr_status basket_american_run(simr_ctx* c, int scheme, const simr_basket& b, const BasketBufs& u, bool want_beta,
                                 hipStream_t s, simr_result* out) {
-  std::vector<int> grids;
+  std::vector<LsmPlace> at(1, LsmPlace{0, 0, -1});
   std::vector<LsmLaunchSet> sets;
-  if (!c->lsm_per_date) sets = lsm_coop_plan({b.paths}, c->num_cus, c->lsm_grid_max, &grids, SIMR_BASKET_NB);
+  if (!c->lsm_per_date) sets = lsm_coop_plan(c->coop_caps, {b.paths}, c->num_cus, c->lsm_grid_max, &at, SIMR_BASKET_NB,
+                                           c->lsm_block == 1024 ? 1024 : 0);
   const bool coop = !sets.empty();  // else one launch per date
   LsmTask t;
   std::memset(&t, 0, sizeof t);
@@ -2124,8 +2120,9 @@ simr_status basket_american_run(simr_ctx* c, int scheme, const simr_basket& b, c
   t.partials = u.partials;
   t.beta64 = want_beta ? u.beta64 : nullptr;
   t.flags = (int32_t*)(u.zero + 1);
-  t.block0 = 0;
-  t.nblocks = coop ? grids[0] : (int)((b.paths + kLsmBlock - 1) / kLsmBlock);
+  t.block0 = at[0].block0;
+  t.nblocks = coop ? at[0].nblocks : (int)((b.paths + kLsmBlock - 1) / kLsmBlock);
+  t.xcd = at[0].xcd;
   simr_status st = basket_upload(c, scheme, b, u, &t, s);
   if (st != SIMR_OK) return st;
   int32_t* flags = (int32_t*)(u.zero + 1);
@@ -2147,8 +2144,7 @@ simr_status basket_american_run(simr_ctx* c, int scheme, const simr_basket& b, c
   {
     Prof pf(c, SIMR_PROF_LSM, s);
     if (coop) {
-      const LsmLaunchSet& ls = sets[0];
-      SIMR_HIP(launch_lsm_coop(u.task, 1, ls.block, ls.ppl, ls.grid, status, s, SIMR_BASKET_NB));
+      SIMR_HIP(launch_lsm_coop(u.task, 1, sets[0], status, s, SIMR_BASKET_NB));
     } else {
       SIMR_HIP(launch_lsm_dates(t.o, u.xs, u.vs, u.fac, u.wcash, u.tau, u.gpart, u.beta32, t.beta64, u.zero + 3,
                                 u.partials, s, SIMR_BASKET_NB));

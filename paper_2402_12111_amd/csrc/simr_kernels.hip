@@ -883,19 +883,33 @@ __global__ __launch_bounds__(64) void lsm_factor_serial_kernel(int32_t chunks, d
 // and later waits give up at once.
 constexpr uint32_t kSpinLimit = 1u << 22;  // passes (a few seconds of polling) before a wait gives up
 
-// Called by a whole wave with the row uniform across it: lane c < NB stores word c, so the row
+// Called by a whole wave, lane c < NB with word c of the row (xchg_word) and storing it, so the row
 // leaves as one write instruction (NB stores issued one after another by a single lane took 6%
 // longer per C2 pricing pass: the readers wait for the last word of every row).
+//   `near`: every block of the task is on this XCD.  The store then stops in the XCD's L2, where
+// the readers' agent-scope loads find it (a store at workgroup scope writes through the L1, and an
+// agent-scope load misses it); otherwise it goes on to memory, where blocks of other XCDs look.
+// A round of 25 or 32 blocks that only exchange takes 0.65 us near and 1.28 us through memory.
 template <int NB>
-__device__ __forceinline__ void xchg_publish(SIMR_GLOBAL unsigned long long* slot, const float (&v)[NB], uint32_t k) {
+__device__ __forceinline__ void xchg_store(SIMR_GLOBAL unsigned long long* slot, int word, float value, uint32_t k,
+                                           bool near) {
+  if (word < NB) {
+    const unsigned long long w = ((unsigned long long)k << 32) | (unsigned long long)__float_as_uint(value);
+    if (near)
+      __hip_atomic_store(slot + word, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else
+      __hip_atomic_store(slot + word, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// Lane c's word of a row that every lane holds.
+template <int NB>
+__device__ __forceinline__ float xchg_word(const float (&v)[NB]) {
   const int lane = threadIdx.x & (kWave - 1);
   float mine = v[0];
 #pragma unroll
   for (int c = 1; c < NB; ++c) mine = lane == c ? v[c] : mine;
-  if (lane < NB) {
-    const unsigned long long w = ((unsigned long long)k << 32) | (unsigned long long)__float_as_uint(mine);
-    __hip_atomic_store(slot + lane, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  return mine;
 }
 
 // Another lane's value of a double (DPP control CTRL within each 16-lane row), both halves moved.
@@ -908,9 +922,9 @@ __device__ __forceinline__ double dpp_term_d(double x) {
 }
 
 // Read by one wave of the pollers: with XW words per block row and GR = 64 / XW groups, lane
-// (c, g) = (lane / GR, lane % GR) polls column c < NB of the rows row0 + g + GR m, m < 8 (all 8
+// (c, g) = (lane / GR, lane % GR) polls column c < NB of the rows row0 + g + GR m, m < M = 8 (all
 // loads of a lane in flight at once, so a pass over the wave's 8 GR rows is one memory round
-// trip), and sums them in FP64 in increasing m; pairwise sums over g ^ 1, g ^ 2 (and g ^ 4) by
+// trip; M = 4 where the task has at most 4 GR rows), and sums them in FP64 in increasing m; pairwise sums over g ^ 1, g ^ 2 (and g ^ 4) by
 // DPP inside the lane's row then leave every lane of column c holding the sum over the wave's
 // rows (lanes c GR .. c GR + GR - 1).  A task of G blocks takes ceil(G / (8 GR)) pollers per
 // block, each on its own 8 GR rows: one wave for up to 64 blocks (32 with 16 words per row), and
@@ -920,7 +934,7 @@ __device__ __forceinline__ double dpp_term_d(double x) {
 // its rows and the next pass follows without a pause.  Redundant pollers (several waves racing
 // over the same rows), or a pause between passes, measured slower: the extra loads contend
 // with the rows being published.
-template <int XW, int NB>
+template <int XW, int NB, int M = 8>
 __device__ __forceinline__ double xchg_gather(const SIMR_GLOBAL unsigned long long* buf, uint32_t G, uint32_t row0, uint32_t k,
                                               int32_t* status) {
   constexpr uint32_t GR = kWave / XW;
@@ -931,9 +945,9 @@ __device__ __forceinline__ double xchg_gather(const SIMR_GLOBAL unsigned long lo
   const SIMR_GLOBAL char* base = (const SIMR_GLOBAL char*)buf;
   // the 32-bit byte offsets of the lane's rows from the uniform base (rows past G read row
   // G - 1, in bounds; their values are not used)
-  uint32_t off[8];
+  uint32_t off[M];
 #pragma unroll
-  for (int m = 0; m < 8; ++m) {
+  for (int m = 0; m < M; ++m) {
     const uint32_t r = row0 + g + GR * m;
     off[m] = ((r < G ? r : G - 1) * XW + c) * (uint32_t)sizeof(unsigned long long);
   }
@@ -943,9 +957,9 @@ __device__ __forceinline__ double xchg_gather(const SIMR_GLOBAL unsigned long lo
       const int32_t failed = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       bool ready = true;
       double s = 0.0;
-      unsigned long long w[8];
+      unsigned long long w[M];
 #pragma unroll
-      for (int m = 0; m < 8; ++m) {
+      for (int m = 0; m < M; ++m) {
         // The empty statement makes the offset a value of this pass, so the address is formed
         // here as scalar base + 32-bit offset.  Otherwise the compiler hoists eight 64-bit
         // addresses out of the loop, 16 registers that 16 waves per CU cannot hold, and their
@@ -956,7 +970,7 @@ __device__ __forceinline__ double xchg_gather(const SIMR_GLOBAL unsigned long lo
                                  __HIP_MEMORY_SCOPE_AGENT);
       }
 #pragma unroll
-      for (int m = 0; m < 8; ++m) {
+      for (int m = 0; m < M; ++m) {
         const bool in = row0 + g + GR * m < G;
         ready &= !in || (uint32_t)(w[m] >> 32) == k;
         s += in ? (double)__uint_as_float((uint32_t)w[m]) : 0.0;
@@ -987,8 +1001,117 @@ __device__ __forceinline__ float row_sum16(float x) {
   return x;
 }
 
+// v of lane l ^ 4, within each row of 16.
+__device__ __forceinline__ float lane_xor4(float v) {
+  const int x = __float_as_int(v);
+  int t = __builtin_amdgcn_update_dpp(0, x, 0x104, 0xF, 0x5, false);  // row_shl:4 into banks 0 and 2
+  t = __builtin_amdgcn_update_dpp(t, x, 0x114, 0xF, 0xA, false);      // row_shr:4 into banks 1 and 3
+  return __int_as_float(t);
+}
+
+// The sums of NV values over each 16-lane row, value q left in the lanes with q in their low bits
+// (lane l of a row holds value l for l < NV): each step adds a lane's partner, l ^ 1, l ^ 2, l ^ 4,
+// l ^ 8, for half of the values only -- a lane keeps one value of a pair and hands the other over --
+// so 6 values take 18 operations where row_sum16 of each takes 24, and one LDS store replaces 6.
+// The additions pair the same lanes in the same order as row_sum16, so the sums are the same bits.
+// One step: lo and hi hold two values; a lane with `upper` keeps hi and gives lo.  (The empty statement
+// keeps the pair in registers of their own: of elements of an array the compiler makes one indexed
+// look-up, a chain of compares.)
+template <class Partner>
+__device__ __forceinline__ float scatter_pair(float lo, float hi, bool upper, Partner partner) {
+  asm("" : "+v"(lo), "+v"(hi));
+  const float keep = upper ? hi : lo, give = upper ? lo : hi;
+  return keep + partner(give);
+}
+
+template <int NV>
+__device__ __forceinline__ float row_sums_scattered(const float (&v)[NV]) {
+  static_assert(NV <= 16, "a value per lane of the row");
+  const int lane = threadIdx.x & (kWave - 1);
+  constexpr int N1 = (NV + 1) / 2, N2 = (N1 + 1) / 2, N3 = (N2 + 1) / 2;
+  static_assert(N3 <= 2, "at most two values before the last step");
+  const auto x1 = [](float t) { return dpp_term<0xB1, 0xF>(t); };  // quad_perm [1,0,3,2]
+  const auto x2 = [](float t) { return dpp_term<0x4E, 0xF>(t); };  // quad_perm [2,3,0,1]
+  const auto x4 = [](float t) { return lane_xor4(t); };
+  const auto x8 = [](float t) { return dpp_term<0x128, 0xF>(t); };  // row_ror:8
+  float r1[N1], r2[N2], r3[N3];
+#pragma unroll
+  for (int i = 0; i < N1; ++i) {
+    if (2 * i + 1 < NV) r1[i] = scatter_pair(v[2 * i], v[2 * i + 1 < NV ? 2 * i + 1 : 0], lane & 1, x1);
+    else r1[i] = v[2 * i] + x1(v[2 * i]);
+  }
+#pragma unroll
+  for (int i = 0; i < N2; ++i) {
+    if (2 * i + 1 < N1) r2[i] = scatter_pair(r1[2 * i], r1[2 * i + 1 < N1 ? 2 * i + 1 : 0], lane & 2, x2);
+    else r2[i] = r1[2 * i] + x2(r1[2 * i]);
+  }
+#pragma unroll
+  for (int i = 0; i < N3; ++i) {
+    if (2 * i + 1 < N2) r3[i] = scatter_pair(r2[2 * i], r2[2 * i + 1 < N2 ? 2 * i + 1 : 0], lane & 4, x4);
+    else r3[i] = r2[2 * i] + x4(r2[2 * i]);
+  }
+  if constexpr (N3 == 2) return scatter_pair(r3[0], r3[1], lane & 8, x8);
+  else return r3[0] + x8(r3[0]);
+}
+
+// The fold of 64 row partials of NV values (s[q 64 + r]) as wave_sum adds them, a lane starting with
+// 8 rows of one value: lane 8 q + g holds value q's sum afterwards (values 8 q' + ... in further
+// passes for NV > 8).  Two 16-byte LDS reads, 7 additions and 3 DPP steps for 8 values, where one
+// row per lane takes 6 DPP steps for each value.
+__device__ __forceinline__ float fold64(const float* __restrict__ s, int q) {
+  const int g = (int)(threadIdx.x & 7u);
+  const float4 u = *reinterpret_cast<const float4*>(s + q * kWave + 8 * g);
+  const float4 v = *reinterpret_cast<const float4*>(s + q * kWave + 8 * g + 4);
+  float t = ((u.x + u.y) + (u.z + u.w)) + ((v.x + v.y) + (v.z + v.w));
+  t += dpp_term<0xB1, 0xF>(t);
+  t += dpp_term<0x4E, 0xF>(t);
+  t += dpp_term<0x141, 0xF>(t);  // row_half_mirror: the other quad
+  return t;
+}
+
 // s_waitcnt vmcnt(0) in the gfx9 encoding (vmcnt 0; expcnt 7 and lgkmcnt 15, which do not wait).
 constexpr int kWaitVmcnt0 = 0x0F70;
+
+constexpr int kHwRegXccId = (31 << 11) | 20;  // s_getreg operand: all 32 bits of HW_REG_XCC_ID
+constexpr uint32_t kXcdTag = 0x80000000u;     // dates are below 2^17
+
+// The task of a block of the induction and the block's number in it; -1 if no task has the block.
+__device__ __forceinline__ int32_t task_of_induction_block(const LsmTask* __restrict__ tasks, int32_t ntasks,
+                                                           uint32_t* blk) {
+  const int32_t lane = (int32_t)(threadIdx.x & (kWave - 1));
+  for (int32_t base = 0; base < ntasks; base += kWave) {
+    const int32_t t = base + lane;
+    bool mine = false;
+    uint32_t b = 0;
+    if (t < ntasks) {
+      const int32_t x = tasks[t].xcd;
+      b = (x < 0 ? blockIdx.x : blockIdx.x / kXcds) - (uint32_t)tasks[t].block0;
+      mine = (x < 0 || x == (int32_t)(blockIdx.x % kXcds)) && b < (uint32_t)tasks[t].nblocks;
+    }
+    const uint64_t m = __ballot(mine);
+    if (m) {
+      const int l = __builtin_ctzll(m);
+      *blk = (uint32_t)__builtin_amdgcn_readlane((int)b, l);
+      return base + l;
+    }
+  }
+  return -1;
+}
+
+// Whether all blocks of a task run on one XCD, by an exchange of its first two words under a tag no
+// date has: the XCD's number x and x^2 through memory, and G sum x^2 = (sum x)^2 exactly if all are
+// equal, the same verdict in every block.  The parity buffer is that of date 2, which a block
+// writes only after every block has left this wait.  Called by one wave; at most one poller's rows.
+template <int XW, int NB>
+__device__ __forceinline__ bool task_on_one_xcd(SIMR_GLOBAL unsigned long long* xchg, uint32_t blk, uint32_t G,
+                                                int32_t* status) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const float x = (float)(__builtin_amdgcn_s_getreg(kHwRegXccId) & 15);
+  xchg_store<NB>(xchg + (size_t)blk * XW, lane, lane == 0 ? x : lane == 1 ? x * x : 0.0f, kXcdTag, false);
+  const double y = xchg_gather<XW, NB>(xchg, G, 0, kXcdTag, status);
+  const double s1 = readlane_d(y, 0), s2 = readlane_d(y, kWave / XW);
+  return s1 * s1 == s2 * (double)G;
+}
 
 // Paths per block fix the induction's bits, the block size does not: a block of BLOCK threads
 // sums its paths as kLsmVBlock virtual lanes (virtual lane s BLOCK + lane holds paths j of the
@@ -1032,18 +1155,15 @@ __global__ __launch_bounds__(BLOCK) void lsm_persistent_kernel(
   // wave-uniform (the compiler does not infer it): the pollers' branch is a scalar branch, not
   // a masked one whose wait counts include the loads of the other branch
   const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-  int32_t t = 0, hi = ntasks - 1;  // the last task whose first block is <= blockIdx.x
-  while (t < hi) {
-    const int32_t mid = (t + hi + 1) >> 1;
-    if (tasks[mid].block0 <= (int32_t)blockIdx.x) t = mid; else hi = mid - 1;
-  }
+  uint32_t blk = 0;
+  const int32_t t = task_of_induction_block(tasks, ntasks, &blk);
+  if (t < 0) return;  // a slot of an XCD that no task takes
   const LsmTask& T = tasks[t];
   const DevOpt o = T.o;
   const SIMR_GLOBAL float* __restrict__ xs = as_global((const float*)T.xs);
   const SIMR_GLOBAL float* __restrict__ vs = as_global((const float*)T.vs);
   const SIMR_GLOBAL double* __restrict__ fac = as_global((const double*)T.fac);
   const uint32_t G = (uint32_t)T.nblocks;
-  const uint32_t blk = blockIdx.x - (uint32_t)T.block0;
   const uint32_t npoll = (G + kRowsPerPoller - 1) / kRowsPerPoller;  // waves 0 .. npoll - 1 poll
   const int N = o.steps;
   const size_t P = (size_t)o.paths;
@@ -1131,7 +1251,7 @@ __global__ __launch_bounds__(BLOCK) void lsm_persistent_kernel(
 #pragma unroll
       for (int a = 0; a < NB; ++a) row[a] = s_red[a * R + lane];
       wave_sum_n<NB>(row);  // the NB folds interleaved
-      xchg_publish<NB>(buf + (size_t)blk * LL::kXW, row, k);
+      xchg_store<NB>(buf + (size_t)blk * LL::kXW, lane, xchg_word<NB>(row), k, false);
     }
     // while the rows travel: evaluate h, a and c of date n - 1, then request date n - 2.  The
     // empty statement takes the new coordinates and hands on the offset, so the requests go out
@@ -1218,6 +1338,258 @@ __global__ __launch_bounds__(BLOCK) void lsm_persistent_kernel(
     for (int j = s; j < PPL; j += S) {
       if (live[j]) {
         const float X = w[j];  // h(S_tau) e^{-r tau dt}
+        k1.add(X);
+        k2.add(X * X);
+        as_global(T.tau)[p0 + j * BLOCK] = tu[j];
+      }
+    }
+    const double v1 = wave_sum(k1.value()), v2 = wave_sum(k2.value());
+    if (lane == 0) {
+      s_red2[s * W + wid] = v1;
+      s_red2[VW + s * W + wid] = v2;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double v1 = s_red2[0], v2 = s_red2[VW];
+    for (int q = 1; q < VW; ++q) {
+      v1 += s_red2[q];
+      v2 += s_red2[VW + q];
+    }
+    as_global(T.partials)[2 * (size_t)blk] = v1;
+    as_global(T.partials)[2 * (size_t)blk + 1] = v2;
+  }
+}
+
+// Waves per SIMD the registers of the relay kernel are held to: 6 (80 registers) at 4 paths per lane,
+// which lets two blocks of 9 waves or three of 5 share a CU.
+constexpr int relay_waves(int ppl, int nb) { return ppl == 4 && nb == 6 ? 6 : 1; }
+
+// The induction of tasks of at most one poller's rows (64 blocks, 32 on 10 functions), with a wave
+// of its own for the exchange: BLOCK threads hold the paths as above, one more wave folds, publishes,
+// polls and solves.  A date is a serial chain -- sums, fold, exchange, solve, exercise -- and a
+// wave that both polls and owns paths lengthens it: its poll loads retire behind the spill rows
+// it has just requested from memory, and its share of the next date's coordinates comes between
+// publishing and polling.  Here the path waves do that work while the relay wave waits, and they
+// take from the chain all that does not need the date's coefficients: the basis products of the
+// next date, masked to the paths in the money (an in-the-money flag becomes a cash flow of -inf
+// that no continuation value is below), so the chain holds one masked product per function, the
+// scattered row sums and one store, then 5 multiply-adds, a compare and two selects per path.
+// The additions and their order are those of lsm_persistent_kernel, so the bits are too.
+// Per date (us, stamps of wave clocks, 25,000 paths on one XCD): exercise and sums to the barrier 0.40,
+// fold and publish 0.27, poll 0.61, solve and barrier 0.10, before the relay wave's priority; of
+// lsm_persistent_kernel there 2.1 in all.  With the priority: 1.25 (1.67 spread over the XCDs).
+template <int BLOCK, int PPL, int NB>
+__global__ __launch_bounds__(BLOCK + kWave, relay_waves(PPL, NB)) void lsm_relay_kernel(const LsmTask* __restrict__ tasks, int32_t ntasks,
+                                                                  int32_t* __restrict__ status) {
+  using LL = LsmLayout<NB>;
+  constexpr int W = BLOCK / kWave;
+  constexpr int S = kLsmVBlock / BLOCK;
+  constexpr int R = kLsmVBlock / 16;
+  constexpr int VW = kLsmVBlock / kWave;
+  constexpr int GR = kWave / LL::kXW;
+  static_assert(kLsmVBlock % BLOCK == 0 && PPL % S == 0 && R == kWave, "whole virtual lanes per lane");
+  __shared__ __align__(16) float s_red[NB * R];
+  __shared__ __align__(16) float s_beta[NB];
+  __shared__ double s_red2[2 * VW];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  uint32_t blk = 0;
+  const int32_t t = task_of_induction_block(tasks, ntasks, &blk);
+  if (t < 0) return;  // a slot of an XCD that no task takes
+  const LsmTask& T = tasks[t];
+  const DevOpt o = T.o;
+  const uint32_t G = (uint32_t)T.nblocks;
+  const int N = o.steps;
+  if (wid == W) {  // the relay wave: issues ahead of the path waves of its SIMD
+    __builtin_amdgcn_s_setprio(3);
+    SIMR_GLOBAL unsigned long long* xchg = as_global(T.xchg);
+    SIMR_GLOBAL unsigned long long* mine = xchg + (size_t)blk * LL::kXW;
+    const SIMR_GLOBAL double* __restrict__ fac = as_global((const double*)T.fac);
+    double* beta64 = T.beta64;
+    const bool near = T.xcd >= 0 && N >= 2 && task_on_one_xcd<LL::kXW, NB>(xchg, blk, G, status);
+    double mrow[NB], grow, mvalid;
+    auto request = [&](int32_t n) {  // lane i < NB: row i of the date's M; e^{r n dt}; the valid flag
+      const SIMR_GLOBAL double* rec = fac + (size_t)n * LL::kRec;
+#pragma unroll
+      for (int c = 0; c < NB; ++c) mrow[c] = lane < NB ? rec[lane * NB + c] : 0.0;
+      grow = rec[LL::kRank + 3];
+      mvalid = rec[LL::kRank + 2];
+    };
+    if (N >= 2) request(N - 1);
+    for (int32_t n = N - 1; n >= 1; --n) {
+      __syncthreads();  // the block's row sums are in LDS
+      const uint32_t k = (uint32_t)(N - n);
+      const size_t parity = (size_t)(k & 1) * G * LL::kXW;
+      // lane 8 q + g stores value q's word (g = 0) and, with more than 8 values, q + 8's (g = 1)
+      const int q = lane >> 3;
+      float sum = fold64(s_red, q < NB ? q : 0);
+      int word = (lane & 7) == 0 ? q : NB;
+      if constexpr (NB > 8) {
+        const float more = fold64(s_red, q + 8 < NB ? q + 8 : 0);
+        if ((lane & 7) == 1) {
+          sum = more;
+          word = q + 8;
+        }
+      }
+      xchg_store<NB>(mine + parity, word, sum, k, near);
+      const double y = G <= 4 * GR ? xchg_gather<LL::kXW, NB, 4>(xchg + parity, G, 0, k, status)
+                                   : xchg_gather<LL::kXW, NB, 8>(xchg + parity, G, 0, k, status);
+      double beta = 0.0;
+#pragma unroll
+      for (int c = 0; c < NB; ++c) beta = __builtin_fma(mrow[c], readlane_d(y, c * GR), beta);
+      beta *= grow;  // the sums are of t_0 values: discount to date n
+      const bool valid = mvalid != 0.0;  // a date without a regression: a continuation nothing exceeds
+      if (lane < NB) s_beta[lane] = valid ? (float)beta : (lane == 0 ? __builtin_inff() : 0.0f);
+      __syncthreads();
+      if (beta64 && blk == 0 && lane < NB) as_global(beta64)[(size_t)n * NB + lane] = valid ? beta : 0.0;
+      request(n >= 2 ? n - 1 : 1);
+    }
+    __syncthreads();  // the block's payoff sums
+    return;
+  }
+  const SIMR_GLOBAL float* __restrict__ xs = as_global((const float*)T.xs);
+  const SIMR_GLOBAL float* __restrict__ vs = as_global((const float*)T.vs);
+  const size_t P = (size_t)o.paths;
+  const uint32_t p0 = blk * (BLOCK * PPL) + threadIdx.x;
+  const float sign = is_call(o.payoff) ? 1.0f : -1.0f;
+  bool live[PPL];
+  uint32_t boff[PPL];
+  float w[PPL];
+  int32_t tu[PPL];
+  const float dN = discount(o, N);
+#pragma unroll
+  for (int j = 0; j < PPL; ++j) {
+    live[j] = p0 + j * BLOCK < (uint32_t)o.paths;
+    boff[j] = (live[j] ? p0 + j * BLOCK : (uint32_t)o.paths - 1) * (uint32_t)sizeof(float);
+    w[j] = live[j] ? intrinsic(o, asset(o, spill_at(xs, (size_t)(N - 1) * P, boff[j]))) * dN : 0.0f;
+    tu[j] = N;
+  }
+  // of the current date: the cash flow (-inf out of the money), its value at t_0 and the basis
+  // functions 1, 2, ... (0 out of the money); raw (x, v) of the next date
+  constexpr int kHeld = PPL <= 2 ? NB : 4;  // lanes of many paths hold a and c and form the products twice
+  float hx[PPL], hd[PPL], ph[PPL][kHeld], xq[PPL], vq[PPL];
+  bool in[PPL];
+  auto coordinates = [&](int j, float x, float v, float dn) {
+    const float d = (live[j] ? asset(o, x) : o.K) - o.K;
+    const float h = sign * d;  // S - K or K - S, exactly
+    in[j] = h > 0.0f;
+    hx[j] = in[j] ? h : -__builtin_inff();
+    hd[j] = h * dn;
+    const float a = in[j] ? d * o.invK : 0.0f;
+    const float c = in[j] ? lsm_c(o, v) : 0.0f;
+    if constexpr (kHeld == NB) {
+      lsm_basis_nb_ac<NB>(a, c, ph[j]);
+    } else {
+      ph[j][1] = a;
+      ph[j][3] = c;
+    }
+  };
+  auto basis = [&](int j, float (&phi)[NB]) {
+    if constexpr (kHeld == NB) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) phi[i] = ph[j][i];
+    } else {
+      lsm_basis_nb_ac<NB>(ph[j][1], ph[j][3], phi);
+    }
+  };
+  {
+    const size_t r2 = (size_t)(N >= 2 ? N - 2 : 0) * P, r3 = (size_t)(N >= 3 ? N - 3 : 0) * P;
+    const float dn = discount(o, N - 1);
+#pragma unroll
+    for (int j = 0; j < PPL; ++j) {
+      coordinates(j, spill_at(xs, r2, boff[j]), spill_at(vs, r2, boff[j]), dn);
+      xq[j] = spill_at(xs, r3, boff[j]);
+      vq[j] = spill_at(vs, r3, boff[j]);
+    }
+  }
+  for (int32_t n = N - 1; n >= 1; --n) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      float acc[NB];
+#pragma unroll
+      for (int j = s; j < PPL; j += S) {
+        float phi[NB];
+        basis(j, phi);
+        const float wi = in[j] ? w[j] : 0.0f;
+        acc[0] = j == s ? wi : acc[0] + wi;
+#pragma unroll
+        for (int a = 1; a < NB; ++a) acc[a] = j == s ? phi[a] * wi : __builtin_fmaf(phi[a], wi, acc[a]);
+      }
+      const float sum = row_sums_scattered<NB>(acc);
+      if ((lane & 15) < NB) s_red[(lane & 15) * R + s * 4 * W + wid * 4 + (lane >> 4)] = sum;
+    }
+    __syncthreads();
+    // while the rows travel: the next date's values aside, then the request of date n - 2 into the
+    // registers just read (the empty statement as in lsm_persistent_kernel).  The empty statements
+    // on both sides keep this work here: before the first barrier it would wait for memory, after
+    // the second it would lengthen the chain.
+#pragma unroll
+    for (int j = 0; j < PPL; ++j) asm volatile("" : "+v"(xq[j]), "+v"(vq[j]));
+    float hx1[PPL], hd1[PPL], ph1[PPL][kHeld];
+    bool in1[PPL];
+    const size_t r3 = (size_t)(n >= 3 ? n - 3 : 0) * P;
+    const float dn1 = discount(o, n - 1);
+#pragma unroll
+    for (int j = 0; j < PPL; ++j) {
+      const float d = (live[j] ? asset(o, xq[j]) : o.K) - o.K;
+      const float h = sign * d;
+      in1[j] = h > 0.0f;
+      hx1[j] = in1[j] ? h : -__builtin_inff();
+      hd1[j] = h * dn1;
+      const float a = in1[j] ? d * o.invK : 0.0f;
+      const float c = in1[j] ? lsm_c(o, vq[j]) : 0.0f;
+      if constexpr (kHeld == NB) {
+        lsm_basis_nb_ac<NB>(a, c, ph1[j]);
+      } else {
+        ph1[j][1] = a;
+        ph1[j][3] = c;
+      }
+      uint32_t b = boff[j];
+      asm volatile("" : "+v"(b) : "v"(hx1[j]), "v"(a), "v"(c));
+      xq[j] = spill_at(xs, r3, b);
+      vq[j] = spill_at(vs, r3, b);
+    }
+#pragma unroll
+    for (int j = 0; j < PPL; ++j) {
+      asm volatile("" : "+v"(hx1[j]), "+v"(hd1[j]));
+      if constexpr (kHeld == NB) {
+#pragma unroll
+        for (int i = 1; i < kHeld; ++i) asm volatile("" : "+v"(ph1[j][i]));
+      }
+    }
+    __syncthreads();
+    float b[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) b[i] = s_beta[i];
+#pragma unroll
+    for (int j = 0; j < PPL; ++j) {
+      float phi[NB];
+      basis(j, phi);
+      float cont = b[0];
+#pragma unroll
+      for (int i = 1; i < NB; ++i) cont = __builtin_fmaf(phi[i], b[i], cont);
+      const bool ex = hx[j] > cont;
+      w[j] = ex ? hd[j] : w[j];
+      tu[j] = ex ? n : tu[j];
+    }
+#pragma unroll
+    for (int j = 0; j < PPL; ++j) {
+      in[j] = in1[j];
+      hx[j] = hx1[j];
+      hd[j] = hd1[j];
+#pragma unroll
+      for (int i = 0; i < kHeld; ++i) ph[j][i] = ph1[j][i];
+    }
+  }
+  // discounted cash flows, in the order of lsm_persistent_kernel
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    Kahan k1, k2;
+#pragma unroll
+    for (int j = s; j < PPL; j += S) {
+      if (live[j]) {
+        const float X = w[j];
         k1.add(X);
         k2.add(X * X);
         as_global(T.tau)[p0 + j * BLOCK] = tu[j];
@@ -2080,6 +2452,31 @@ static int lsm_coop_capacity() {
 }
 
 template <int BLOCK, int PPL, int NB>
+static int lsm_relay_capacity() {
+  int nb = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, lsm_relay_kernel<BLOCK, PPL, NB>, BLOCK + kWave, 0) !=
+      hipSuccess)
+    return 0;
+  // That count is of waves per CU.  A block of 4 q + 1 waves puts q + 1 on one of the 4 SIMDs, and
+  // blocks may pick the same one, so count q + 1 waves on every SIMD.
+  hipFuncAttributes fa;
+  if (hipFuncGetAttributes(&fa, (const void*)lsm_relay_kernel<BLOCK, PPL, NB>) != hipSuccess || fa.numRegs < 1)
+    return 0;
+  const int per_simd = std::min(8, 512 / ((fa.numRegs + 7) / 8 * 8));
+  return std::min(nb, per_simd / (BLOCK / kWave / 4 + 1));
+}
+
+template <int BLOCK, int PPL, int NB>
+static hipError_t launch_lsm_relay_t(const LsmTask* tasks, int ntasks, int grid, int32_t* status, hipStream_t s) {
+  const LsmTask* a0 = tasks;
+  int32_t a1 = ntasks;
+  int32_t* a2 = status;
+  void* args[] = {&a0, &a1, &a2};
+  return hipLaunchCooperativeKernel((const void*)lsm_relay_kernel<BLOCK, PPL, NB>, dim3(grid), dim3(BLOCK + kWave),
+                                    args, 0, s);
+}
+
+template <int BLOCK, int PPL, int NB>
 static hipError_t launch_lsm_coop_t(const LsmTask* tasks, int ntasks, int grid, int32_t* status, hipStream_t s) {
   const LsmTask* a0 = tasks;
   int32_t a1 = ntasks;
@@ -2091,13 +2488,23 @@ static hipError_t launch_lsm_coop_t(const LsmTask* tasks, int ntasks, int grid, 
 
 // Shapes of the cooperative induction: an option's paths per block, kLsmVBlock x 1, 2 or 4
 // (most latency-tolerant first: fewer paths per lane, more waves per CU), fix its grid and its
-// bits.  A launch runs them on 1024-thread blocks, or on 256-thread blocks with 4x the paths
-// per lane (the same bits), which fit more blocks per CU.  The 10-function basis keeps the
-// 1024-thread blocks (its per-path basis values live in registers across the exchange).
+// bits.  A launch runs them on one of four layouts, all with the same bits:
+//   relay512, relay256  512 or 256 path threads and a relay wave (lsm_relay_kernel): options of at
+//                       most one poller's rows;
+//   1024, 256           the pollers among the path waves (lsm_persistent_kernel).
+// The 10-function basis has relay512 at 1 path per virtual lane, and 1024.
 static const int kCoopPpl[] = {1, 2, 4};
 constexpr int kCoopShapes = 3;
 
-static int coop_capacity(int block, int ppl, int nb) {
+static int coop_capacity(int block, int ppl, int nb, bool relay) {
+  if (relay) {
+    if (nb == 10) return block == 512 && ppl == 2 ? lsm_relay_capacity<512, 2, 10>() : 0;
+    if (block == 512 && ppl == 2) return lsm_relay_capacity<512, 2, 6>();
+    if (block == 512 && ppl == 4) return lsm_relay_capacity<512, 4, 6>();
+    if (block == 512 && ppl == 8) return lsm_relay_capacity<512, 8, 6>();
+    if (block == 256 && ppl == 4) return lsm_relay_capacity<256, 4, 6>();
+    return 0;
+  }
   if (nb == 10) {
     if (block == 1024 && ppl == 1) return lsm_coop_capacity<1024, 1, 10>();
     if (block == 1024 && ppl == 2) return lsm_coop_capacity<1024, 2, 10>();
@@ -2113,21 +2520,80 @@ static int coop_capacity(int block, int ppl, int nb) {
   return 0;
 }
 
+namespace {
+// One layout's share of a run of options: the first `near` of them on one XCD each, the next `far` on
+// the blocks behind those.
+struct CoopFit {
+  int block, ppl;
+  bool relay;
+  int near = 0, far = 0, grid = 0;
+  std::vector<LsmPlace> at;
+};
+
+// As many of the options with these block counts as fit `cap` co-resident blocks.  Relay layouts put
+// each option on the XCD with the fewest blocks so far while it fits there, then spread options
+// over the blocks that are left.
+CoopFit coop_fit(const std::vector<int>& nblocks, int block, int ppl, bool relay, int cap, int num_cus, int rows) {
+  CoopFit f{block, ppl, relay};
+  const size_t n = nblocks.size();
+  if (relay && num_cus % kXcds == 0) {
+    int used[kXcds] = {};
+    // alone, and two or more paths per virtual lane: sharing its XCD's CUs costs what the nearer
+    // exchange gains (131,072 paths: 507 us near, 496 spread; 65,536 paths 424 and 459)
+    const bool alone = n == 1 && ppl * block > kLsmVBlock && nblocks[0] > num_cus / kXcds;
+    while (!alone && f.at.size() < n && nblocks[f.at.size()] <= rows) {
+      const int x = (int)(std::min_element(used, used + kXcds) - used);
+      const int m = nblocks[f.at.size()];
+      if (used[x] + m > cap / kXcds) break;
+      f.at.push_back(LsmPlace{m, used[x], x});
+      used[x] += m;
+    }
+    f.near = (int)f.at.size();
+    f.grid = kXcds * *std::max_element(used, used + kXcds);
+  }
+  while (f.at.size() < n && f.grid + nblocks[f.at.size()] <= cap && (!relay || nblocks[f.at.size()] <= rows)) {
+    const int m = nblocks[f.at.size()];
+    f.at.push_back(LsmPlace{m, f.grid, -1});
+    f.grid += m;
+  }
+  f.far = (int)f.at.size() - f.near;
+  return f;
+}
+}  // namespace
+
 // Every option takes the shape it would take alone: the first whose grid fits within gmax
 // blocks, else within 256.  Consecutive options of one shape then share launches while their
-// blocks fit co-resident, on whichever block size holds more of them (1024 threads on a tie,
-// or the size `block` names if nonzero and the option fits it).  An option's result therefore
-// depends neither on the others nor on the block size.
-std::vector<LsmLaunchSet> lsm_coop_plan(const std::vector<int64_t>& paths, int num_cus, int gmax,
-                                        std::vector<int>* grids, int nb, int block) {
-  if (nb != 6) block = 1024;
-  int cap[2][kCoopShapes];  // co-resident blocks: [0] 1024 threads, [1] 256 threads
-  for (int q = 0; q < kCoopShapes; ++q) {
-    cap[0][q] = block == 256 ? 0 : coop_capacity(1024, kCoopPpl[q], nb) * num_cus;
-    cap[1][q] = block == 1024 ? 0 : coop_capacity(256, 4 * kCoopPpl[q], nb) * num_cus;
+// blocks fit co-resident, on the layout that holds more of them; of equals the one with fewer
+// spread over the XCDs, then the first of relay512, relay256, 1024, 256.  An option's result
+// depends neither on the others nor on the layout.  Induction of one launch (us, one option of 25,000
+// paths x 252 dates unless said): relay512 near 314, spread 421, relay256 near 356, spread 458; 1024
+// 532.  20 options: relay256 near 519, relay512 spread 628, 256 799.  30 options x 504 dates:
+// relay256 1,500 spread, 256 1,919.  One of 131,072 paths: relay512 496, 1024 559; 8 of them relay512 near
+// 629, 256 918; one of 262,144: 641, 719.
+struct CoopLayout { int block; bool relay; };
+static const CoopLayout kLayouts[] = {{512, true}, {256, true}, {1024, false}, {256, false}};
+
+CoopCaps lsm_coop_caps() {
+  CoopCaps c;
+  for (int b = 0; b < 2; ++b)
+    for (int z = 0; z < 4; ++z)
+      for (int q = 0; q < kCoopShapes; ++q)
+        c.per_cu[b][z][q] = coop_capacity(kLayouts[z].block, kCoopPpl[q] * (kLsmVBlock / kLayouts[z].block),
+                                          b ? 10 : 6, kLayouts[z].relay);
+  return c;
+}
+
+std::vector<LsmLaunchSet> lsm_coop_plan(const CoopCaps& caps_of, const std::vector<int64_t>& paths, int num_cus,
+                                        int gmax, std::vector<LsmPlace>* places, int nb, int block) {
+  const int rows = 8 * kWave / (nb == 6 ? LsmLayout<6>::kXW : LsmLayout<10>::kXW);  // of one poller
+  int cap[4][kCoopShapes];  // co-resident blocks of each layout and shape
+  for (int z = 0; z < 4; ++z) {
+    const CoopLayout& l = kLayouts[z];
+    const bool use = block == 0 || (!l.relay && l.block == block);
+    for (int q = 0; q < kCoopShapes; ++q) cap[z][q] = use ? caps_of.per_cu[nb == 10][z][q] * num_cus : 0;
   }
   const int n = (int)paths.size();
-  grids->assign(n, 0);
+  places->assign(n, LsmPlace{0, 0, -1});
   std::vector<int> shape(n, -1);
   for (int i = 0; i < n; ++i) {
     const int64_t caps[2] = {std::min(gmax, 256), 256};
@@ -2135,9 +2601,9 @@ std::vector<LsmLaunchSet> lsm_coop_plan(const std::vector<int64_t>& paths, int n
       for (int q = 0; q < kCoopShapes && shape[i] < 0; ++q) {
         const int64_t per = (int64_t)kLsmVBlock * kCoopPpl[q];
         const int64_t g = (paths[i] + per - 1) / per;
-        if (g <= std::min<int64_t>(std::max(cap[0][q], cap[1][q]), caps[pass])) {
+        if (g <= std::min<int64_t>(std::max(cap[2][q], cap[3][q]), caps[pass])) {
           shape[i] = q;
-          (*grids)[i] = (int)g;
+          (*places)[i].nblocks = (int)g;
         }
       }
     if (shape[i] < 0) return {};
@@ -2145,16 +2611,19 @@ std::vector<LsmLaunchSet> lsm_coop_plan(const std::vector<int64_t>& paths, int n
   std::vector<LsmLaunchSet> sets;
   for (int i = 0; i < n;) {
     const int q = shape[i];
-    int count[2] = {0, 0}, grid[2] = {0, 0};
-    for (int z = 0; z < 2; ++z)
-      while (i + count[z] < n && shape[i + count[z]] == q && grid[z] + (*grids)[i + count[z]] <= cap[z][q]) {
-        grid[z] += (*grids)[i + count[z]];
-        ++count[z];
-      }
-    const int z = count[1] > count[0] ? 1 : 0;
-    LsmLaunchSet ls{i, count[z], z ? 256 : 1024, z ? 4 * kCoopPpl[q] : kCoopPpl[q], grid[z]};
-    sets.push_back(ls);
-    i += count[z];
+    std::vector<int> run;  // the blocks of the options from i on that share its shape
+    for (int k = i; k < n && shape[k] == q; ++k) run.push_back((*places)[k].nblocks);
+    CoopFit best{0, 0, false};
+    for (int z = 0; z < 4; ++z) {
+      const CoopLayout& l = kLayouts[z];
+      CoopFit f = coop_fit(run, l.block, kCoopPpl[q] * (kLsmVBlock / l.block), l.relay, cap[z][q], num_cus, rows);
+      const size_t have = best.at.size();
+      if (f.at.size() > have || (f.relay && f.at.size() == have && f.far < best.far)) best = f;
+    }
+    if (best.at.empty()) return {};
+    for (size_t k = 0; k < best.at.size(); ++k) (*places)[i + k] = best.at[k];
+    sets.push_back(LsmLaunchSet{i, (int)best.at.size(), best.block, best.ppl, best.grid, best.relay});
+    i += (int)best.at.size();
   }
   return sets;
 }
@@ -2195,8 +2664,18 @@ hipError_t launch_lsm_factor(const DevOpt& o, double rdt, const float* gram, dou
 }
 
 // The cooperative induction over all dates of every task (factors from launch_lsm_factor).
-hipError_t launch_lsm_coop(const LsmTask* tasks, int ntasks, int block, int ppl, int grid, int32_t* status,
-                           hipStream_t s, int nb) {
+hipError_t launch_lsm_coop(const LsmTask* tasks, int ntasks, const LsmLaunchSet& ls, int32_t* status, hipStream_t s,
+                           int nb) {
+  const int block = ls.block, ppl = ls.ppl, grid = ls.grid;
+  if (ls.relay) {
+    if (nb == 10 && block == 512 && ppl == 2) return launch_lsm_relay_t<512, 2, 10>(tasks, ntasks, grid, status, s);
+    if (nb != 6) return hipErrorInvalidValue;
+    if (block == 512 && ppl == 2) return launch_lsm_relay_t<512, 2, 6>(tasks, ntasks, grid, status, s);
+    if (block == 512 && ppl == 4) return launch_lsm_relay_t<512, 4, 6>(tasks, ntasks, grid, status, s);
+    if (block == 512 && ppl == 8) return launch_lsm_relay_t<512, 8, 6>(tasks, ntasks, grid, status, s);
+    if (block == 256 && ppl == 4) return launch_lsm_relay_t<256, 4, 6>(tasks, ntasks, grid, status, s);
+    return hipErrorInvalidValue;
+  }
   if (nb == 10) {
     if (block == 1024 && ppl == 1) return launch_lsm_coop_t<1024, 1, 10>(tasks, ntasks, grid, status, s);
     if (block == 1024 && ppl == 2) return launch_lsm_coop_t<1024, 2, 10>(tasks, ntasks, grid, status, s);

@@ -56,7 +56,8 @@ struct LsmTask {
   double* partials;          // out: {sum X, sum X^2} per block of the task
   double* beta64;            // out, may be null: the 6 FP64 coefficients per date (first block)
   int32_t* flags;            // SIMR_LSM_FEW_ITM | SIMR_LSM_DROPPED of the option (read by the finish)
-  int32_t block0, nblocks;
+  int32_t block0, nblocks;   // its first block and their count (of the induction)
+  int32_t xcd;               // >= 0: block b of the task is block (block0 + b) kXcds + xcd of the launch
   // the batched launches over all tasks of a pass (spill, Gram pre-pass, factors, adjoints):
   // task t's blocks [first, first + count) of each
   float* gram;               // Gram sums of every (date, chunk)
@@ -86,18 +87,26 @@ constexpr int kLsmGramRow10 = 56;
 constexpr int kLsmFacRec10 = 128;
 constexpr int kLsmXchgWords10 = 2 * 256 * 16;
 
+constexpr int kXcds = 8;  // workgroup i of a launch goes to XCD i mod 8 (32 CUs with one L2 each)
+
 // Cooperative launches of a list of American options: consecutive tasks [first, first + count)
-// share one launch of `block` threads x `ppl` paths per lane.
-struct LsmLaunchSet { int first, count, block, ppl, grid; };
+// share one launch of blocks of `block` path threads x `ppl` paths per lane (relay: and one wave
+// for the exchange).
+struct LsmLaunchSet { int first, count, block, ppl, grid; bool relay; };
+// Where an option's blocks are in its launch: [block0, block0 + nblocks), or with xcd >= 0 the
+// blocks (block0 + b) kXcds + xcd, b < nblocks, which share an XCD.
+struct LsmPlace { int nblocks, block0, xcd; };
+// Blocks per CU of each layout of the induction: [6 or 10 functions][layout][paths per block].
+struct CoopCaps { int per_cu[2][4][3]; };
+CoopCaps lsm_coop_caps();  // of the current device
 // Splits options with the given path counts into launch sets whose blocks are co-resident, each
 // option taking ceil(P / (1024 ppl)) blocks of the paths per block it would take alone (at most
-// `gmax` blocks if possible, else 256), run as 1024 threads x ppl or 256 threads x 4 ppl (the
-// same bits).  Returns the sets; empty if some option fits no shape.  grids[i] receives option
-// i's blocks.  nb: functions of the regression basis (6, or 10 for baskets: 1024-thread blocks
-// only).  block: 0 lets each set take the block size that holds more of its options; 1024 or
-// 256 restricts every set to that size.
-std::vector<LsmLaunchSet> lsm_coop_plan(const std::vector<int64_t>& paths, int num_cus, int gmax,
-                                        std::vector<int>* grids, int nb = 6, int block = 0);
+// `gmax` blocks if possible, else 256), run on the layout that holds more of them (the same bits).
+// Returns the sets; empty if some option fits no shape.  places[i] receives option i's blocks.
+// nb: functions of the regression basis (6, or 10 for baskets).  block: 0 for any layout; 1024 or
+// 256 restricts every set to blocks of that size without a relay wave.
+std::vector<LsmLaunchSet> lsm_coop_plan(const CoopCaps& caps, const std::vector<int64_t>& paths, int num_cus, int gmax,
+                                        std::vector<LsmPlace>* places, int nb = 6, int block = 0);
 // The Gram and right-hand-side sums of every date, then (launch_lsm_factor, same stream) their
 // FP64 factorisations; rdt = r T / N in FP64 (the factor records carry e^{r n dt}).
 hipError_t launch_lsm_gram(const DevOpt& o, const float* xs, const float* vs, float* gram, hipStream_t s,
@@ -111,8 +120,8 @@ hipError_t launch_spill_tasks(int scheme, const LsmTask* tasks, int ntasks, int 
 hipError_t launch_gram_tasks(const LsmTask* tasks, int ntasks, int grid, hipStream_t s);
 hipError_t launch_factor_tasks(const LsmTask* tasks, int ntasks, int grid, hipStream_t s);
 // tasks: device array, sorted by block0, block0 relative to this launch.
-hipError_t launch_lsm_coop(const LsmTask* tasks, int ntasks, int block, int ppl, int grid, int32_t* status,
-                           hipStream_t s, int nb = 6);
+hipError_t launch_lsm_coop(const LsmTask* tasks, int ntasks, const LsmLaunchSet& ls, int32_t* status, hipStream_t s,
+                           int nb = 6);
 // out[2 t], out[2 t + 1] = sums of task t's block partials in block order (FP64); then, as int32
 // after the 2 ntasks doubles: the flags of every task, then *status.
 hipError_t launch_finalize_tasks(const LsmTask* tasks, int ntasks, const int32_t* status, double* out,
