@@ -97,9 +97,11 @@ __device__ __forceinline__ Words philox4x32_10(uint32_t c0, uint32_t c1, uint32_
   return Words{c0, c1, c2, c3};
 }
 
-// ((w >> 9) + 1/2) * 2^-23: the odd multiples of 2^-24 in (0,1), exact in FP32 (and 1 - u too).
+// ((w >> 9) + 1/2) * 2^-23: the odd multiples of 2^-24 in (0,1), exact in FP32 (and 1 - u too).  One
+// funnel shift puts the 23 bits under the exponent of 1.0, and f - (1 - 2^-24) is exact: two
+// instructions where shift, conversion and multiply-add took three.
 __device__ __forceinline__ float u01(uint32_t w) {
-  return __builtin_fmaf((float)(w >> 9), 0x1p-23f, 0x1p-24f);
+  return __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, w, 9u)) - 0x1.fffffep-1f;
 }
 
 // Box-Muller with the hardware transcendentals: v_log_f32 is log2, and v_sin_f32 / v_cos_f32
