@@ -1835,7 +1835,7 @@ simr_status simr_debug_lsm(simr_ctx* ctx, const simr_option* opt, const simr_par
 namespace {
 
 // Workspace sizes are computed without a context: sized for the larger block count of either
-// launch layout (the split layout has up to 32x the blocks), whatever the device.
+// launch layout (the wave kernel has up to 32x the blocks), whatever the device.
 constexpr int kWorkspaceCus = 1 << 20;
 
 bool basket_american(const simr_basket& b) { return b.payoff == SIMR_AMER_PUT || b.payoff == SIMR_AMER_CALL; }
@@ -2003,12 +2003,11 @@ struct BasketBufs {
   uint32_t* zero;    // [0] unused, [1] flags, [2] status, [3] per-date ticket, [16 ...) exchange words
   int64_t zero_words;
   int nblk, nchunk;
-  int lpp;           // lanes per path of the basket kernels
+  BasketLayout lay[3];  // of the basket kernels, by mode
 };
 
 BasketBufs carve_basket(Carve& cv, const simr_basket& b, int op, int num_cus) {
-  BasketBufs u;
-  std::memset(&u, 0, sizeof u);
+  BasketBufs u{};
   const int d = b.assets;
   const int64_t P = b.paths;
   const int N = b.steps;
@@ -2021,8 +2020,8 @@ BasketBufs carve_basket(Carve& cv, const simr_basket& b, int op, int num_cus) {
   u.ao = u.upload ? (DevOpt*)(u.upload + u.off_opts) : nullptr;
   u.task = u.upload ? (LsmTask*)(u.upload + u.off_task) : nullptr;
   u.dl = (u.upload && op == 3) ? (float*)(u.upload + u.off_dl) : nullptr;
-  u.lpp = basket_lanes_per_path(d, P, num_cus);
-  u.nblk = (int)((P * u.lpp + 255) / 256);  // blocks of 256 / lpp paths
+  for (int m = 0; m < 3; ++m) u.lay[m] = basket_layout(m, d, P, num_cus);
+  u.nblk = u.lay[0].blocks;
   u.nchunk = (int)((P + kBasketChunk - 1) / kBasketChunk);
   u.rows = cv.take<double>((size_t)u.nblk * 2);
   u.sums = cv.take<double>((size_t)std::max(std::max(2, basket_ncol(d)), 2 * risk_cols(d)));
@@ -2129,7 +2128,7 @@ simr_status basket_american_run(simr_ctx* c, int scheme, const simr_basket& b, c
   int32_t* status = (int32_t*)(u.zero + 2);
   {
     Prof pf(c, SIMR_PROF_SPILL, s);
-    SIMR_HIP(launch_basket_paths(scheme, 2, b.assets, b.paths, u.lpp, u.bk, u.ao, nullptr, u.xs, u.vs, nullptr, u.zero,
+    SIMR_HIP(launch_basket_paths(scheme, 2, b.assets, b.paths, u.lay[2], u.bk, u.ao, nullptr, u.xs, u.vs, nullptr, u.zero,
                                  u.zero_words, nullptr, s));
   }
   if (c->lsm_fail_test && coop) SIMR_HIP(hipMemsetD32Async((hipDeviceptr_t)status, 1u, 1, s));
@@ -2201,7 +2200,7 @@ simr_status basket_european_run(simr_ctx* c, int scheme, const simr_basket& b, c
   if (st != SIMR_OK) return st;
   {
     Prof pf(c, SIMR_PROF_PRICE, s);
-    SIMR_HIP(launch_basket_paths(scheme, 0, b.assets, b.paths, u.lpp, u.bk, u.ao, nullptr, d_xT, d_vT, d_pay, nullptr, 0,
+    SIMR_HIP(launch_basket_paths(scheme, 0, b.assets, b.paths, u.lay[0], u.bk, u.ao, nullptr, d_xT, d_vT, d_pay, nullptr, 0,
                                  u.rows, s));
   }
   SIMR_HIP(launch_finalize_rows(u.rows, 2, nullptr, 0, u.nblk, u.sums, s));
@@ -2286,7 +2285,7 @@ simr_status simr_basket_greeks(simr_ctx* ctx, const simr_basket* b, const simr_p
   const int ncol = am ? 2 + 2 * d : basket_ncol(d);
   {
     Prof pf(ctx, SIMR_PROF_PRICE, s);
-    SIMR_HIP(launch_basket_paths(scheme, 1, d, b->paths, u.lpp, u.bk, u.ao, am ? u.tau : nullptr, u.rec, nullptr, nullptr,
+    SIMR_HIP(launch_basket_paths(scheme, 1, d, b->paths, u.lay[1], u.bk, u.ao, am ? u.tau : nullptr, u.rec, nullptr, nullptr,
                                  nullptr, 0, nullptr, s));
   }
   SIMR_HIP(launch_basket_moments(u.bk, b->paths, u.rec, ncol, u.part, s));

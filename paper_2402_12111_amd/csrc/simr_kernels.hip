@@ -3175,158 +3175,237 @@ __global__ __launch_bounds__(256) void basket_path_kernel(const DevBasket* __res
   }
 }
 
-// Few paths, many assets: LPP consecutive lanes of a wave per path, lane s of a path owning the
-// assets [s A, s A + A), A = DMAX / LPP, so that small path counts still fill the chip.  The
-// per-asset constants, L and L^{-1} are copied to LDS (the asset indices differ between lanes);
-// the independent asset normals of a step pass through LDS; the basket sums are folded across
-// the path's lanes by shuffles.  Every lane runs all N steps (dead lanes and, in MODE 1, paths
-// past their stopping index draw but do not step), so the two block barriers per step are
-// uniform.  Modes and outputs as basket_path_kernel (the FP32 basket sums are added in another
-// order, a rounding-level difference).
-template <int SCHEME, int DMAX, int LPP, int MODE>
-__global__ __launch_bounds__(256) void basket_split_kernel(const DevBasket* __restrict__ bk,
-                                                           const DevOpt* __restrict__ ao,
-                                                           const int32_t* __restrict__ tau, float* __restrict__ o1,
-                                                           float* __restrict__ o2, float* __restrict__ o3,
-                                                           uint32_t* __restrict__ zero, int64_t nzero,
-                                                           double* __restrict__ rows) {
-  constexpr int A = DMAX / LPP;
-  constexpr int PB = 256 / LPP;  // paths per block
-  static_assert(kWave % LPP == 0 && DMAX % LPP == 0, "a path's lanes lie in one wave");
-  __shared__ DevOpt s_ao[DMAX];
-  __shared__ float s_L[DMAX * (DMAX + 1) / 2];
-  __shared__ float s_Li[MODE == 1 ? DMAX * (DMAX + 1) / 2 : 1];
-  __shared__ float s_z[PB * (DMAX + 1)];
+// One or two assets per lane: a wave takes PPW = 64 / L paths, L = ceil(d / A) consecutive lanes
+// each, of any count (10 lanes for 20 assets: 60 of 64 busy).  A lane holds its assets' step constants
+// and rows of L (in MODE 1 columns of L^{-1}) in registers, where one path per lane reloads them as
+// scalars every step (8 assets alone need 130 of the 102 there are); a path's lanes are of one
+// wave, so the step's normals pass through LDS without a block barrier, read four at a time.  Bound
+// by VALU issue, and by latency below 2 waves per SIMD.  It replaces a kernel with a power of two
+// lanes per path, L, its rows and the constants in LDS (two reads per term of L z) and two barriers
+// per step: 20 assets, 25,000 paths x 252 steps, price 1,148 -> 603 us, Greeks 2,167 -> 944,
+// American price 2,020 -> 1,199; and one path per lane: 8 assets, 25,000 x 126, price 522 -> 147,
+// 262,144 x 63 Greeks 550 -> 447.
+//   The basket sums add the assets in the order of BasketLayout::leaf: LEAFA = 0, one after another
+// in asset order (as basket_path_kernel); else leaves of LEAFA consecutive assets one after another,
+// then the DMAX / LEAFA leaves pairwise (leaf q with q ^ 1, those with q ^ 2, ...).
+// Modes and outputs as basket_path_kernel; rows: 2 doubles per block of 4 PPW paths.
+__device__ __forceinline__ void wave_fence() {  // LDS writes of the wave before its later LDS reads
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+template <int SCHEME, int DMAX, int A, int LEAFA, int MODE>
+__global__ __launch_bounds__(256) void basket_wave_kernel(const DevBasket* __restrict__ bk,
+                                                          const DevOpt* __restrict__ ao,
+                                                          const int32_t* __restrict__ tau, float* __restrict__ o1,
+                                                          float* __restrict__ o2, float* __restrict__ o3,
+                                                          uint32_t* __restrict__ zero, int64_t nzero,
+                                                          double* __restrict__ rows) {
+  constexpr int DMIN = DMAX == 8 ? 3 : DMAX / 2 + 1;        // assets this instance is used for
+  constexpr int ROWS = kWave / ((DMIN + A - 1) / A) + 1;    // a wave's paths, and a row for idle lanes
+  constexpr int ZS = DMAX + 4;                              // floats per row of normals: no bank conflicts
+  constexpr int LEAVES = LEAFA ? DMAX / LEAFA : 0;
+  constexpr int Q0 = LEAFA == A ? 0 : DMAX;                 // a row: the assets' pairs (none if a lane is a leaf),
+  constexpr int SS = LEAVES ? Q0 + LEAVES + (LEAVES + 3) / 4 * 2 : DMAX;  // the leaves' and the leaf quads'
+  static_assert(LEAVES == 0 || (LEAVES % 4 == 0 && LEAVES <= DMIN / A + 1 + DMAX * (LEAFA == A)), "a lane per leaf");
+  __shared__ __align__(16) float s_z[4][ROWS * ZS];
+  __shared__ __align__(16) float2 s_s[4][ROWS * SS];
   const DevBasket& B = *bk;
   const int d = B.d;
-  const int t = threadIdx.x;
   if constexpr (MODE == 2) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + t; i < nzero; i += (int64_t)gridDim.x * 256) zero[i] = 0u;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nzero; i += (int64_t)gridDim.x * 256) zero[i] = 0u;
   }
-  {
-    const uint32_t* src = (const uint32_t*)ao;
-    uint32_t* dst = (uint32_t*)s_ao;
-    const int nw = d * (int)(sizeof(DevOpt) / 4);
-    for (int w = t; w < nw; w += 256) dst[w] = src[w];
-    const int nt = d * (d + 1) / 2;
-    for (int w = t; w < nt; w += 256) {
-      s_L[w] = B.L[w];
-      if constexpr (MODE == 1) s_Li[w] = B.Linv[w];
-    }
-  }
-  __syncthreads();
-  const int pl = t / LPP, sub = t % LPP;
-  const uint32_t p = blockIdx.x * PB + pl;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int L = (d + A - 1) / A, PPW = kWave / L;
+  const int pl = min(lane / L, PPW), sub = lane - pl * L;  // idle lanes: row PPW
+  const uint32_t p = (blockIdx.x * 4 + (uint32_t)wid) * (uint32_t)PPW + (uint32_t)pl;
   const size_t P = (size_t)B.paths;
-  const bool live = p < (uint32_t)B.paths;
+  const bool live = pl < PPW && p < (uint32_t)B.paths;
+  float* zrow = s_z[wid] + pl * ZS;
+  float2* srow = s_s[wid] + pl * SS;
   const int i0 = sub * A;
+  DevOpt o[A];
+  float Lr[A][DMAX], Li[MODE == 1 ? A : 1][MODE == 1 ? DMAX : 1], wS0[A];
+  bool has[A];
   float x[A], v[A], sa[A], sb[A];
 #pragma unroll
   for (int j = 0; j < A; ++j) {
+    has[j] = i0 + j < d && pl < PPW;
+    const int i = has[j] ? i0 + j : 0;  // lanes without an asset step asset 0 and are not read
+    o[j] = ao[i];
+    wS0[j] = has[j] ? B.wS0[i] : 0.0f;
     x[j] = 0.0f;
-    v[j] = i0 + j < d ? s_ao[i0 + j].v0 : 0.0f;
+    v[j] = o[j].v0;
     sa[j] = 0.0f;
     sb[j] = 0.0f;
+#pragma unroll
+    for (int k = 0; k < DMAX; ++k) {
+      Lr[j][k] = k <= i ? B.L[tri(i) + (k <= i ? k : 0)] : 0.0f;
+      if constexpr (MODE == 1) Li[j][k] = k >= i && k < d ? B.Linv[tri(k) + i] : 0.0f;
+    }
   }
+  for (int q = sub; q < ZS; q += L) zrow[q] = 0.0f;
+  for (int q = sub; q < SS; q += L) srow[q] = make_float2(0.0f, 0.0f);
+  wave_fence();
+  // the basket's pair of sums from the lanes' (S, v): valid in the lanes with sub = 0
+  auto basket_sums = [&](const float (&S)[A], const float (&vm)[A], float& Bn, float& Bv) {
+    if constexpr (LEAVES == 0) {
+#pragma unroll
+      for (int j = 0; j < A; ++j)
+        if (has[j]) srow[i0 + j] = make_float2(S[j], vm[j]);
+      wave_fence();
+      Bn = 0.0f;
+      Bv = 0.0f;
+      if (sub == 0) {
+#pragma unroll
+        for (int i = 0; i < DMAX; ++i) {
+          if (i < d) {
+            const float2 t = srow[i];
+            Bn += t.x;
+            Bv = __builtin_fmaf(t.x, t.y, Bv);
+          }
+        }
+      }
+    } else {
+      float bn = 0.0f, bv = 0.0f;
+      if constexpr (LEAFA == A) {
+#pragma unroll
+        for (int j = 0; j < A; ++j) {
+          if (has[j]) {
+            bn += S[j];
+            bv = __builtin_fmaf(S[j], vm[j], bv);
+          }
+        }
+        if (pl < PPW) srow[sub] = make_float2(bn, bv);
+      } else {
+#pragma unroll
+        for (int j = 0; j < A; ++j)
+          if (has[j]) srow[i0 + j] = make_float2(S[j], vm[j]);
+        wave_fence();
+        if (sub < LEAVES) {
+#pragma unroll
+          for (int q = 0; q < LEAFA; ++q) {  // assets past the last hold (0, 0)
+            const float2 t = srow[sub * LEAFA + q];
+            bn += t.x;
+            bv = __builtin_fmaf(t.x, t.y, bv);
+          }
+          srow[Q0 + sub] = make_float2(bn, bv);
+        }
+      }
+      wave_fence();
+      if (sub < LEAVES / 4) {
+        const float4 a = *reinterpret_cast<const float4*>(srow + Q0 + 4 * sub);
+        const float4 b = *reinterpret_cast<const float4*>(srow + Q0 + 4 * sub + 2);
+        srow[Q0 + LEAVES + sub] = make_float2((a.x + a.z) + (b.x + b.z), (a.y + a.w) + (b.y + b.w));
+      }
+      wave_fence();
+      Bn = 0.0f;
+      Bv = 0.0f;
+      if (sub == 0) {
+        float2 q[LEAVES / 4];
+#pragma unroll
+        for (int t = 0; t < LEAVES / 4; ++t) q[t] = srow[Q0 + LEAVES + t];
+#pragma unroll
+        for (int w = 1; w < LEAVES / 4; w *= 2)
+#pragma unroll
+          for (int t = 0; t + w < LEAVES / 4; t += 2 * w) {
+            q[t].x += q[t + w].x;
+            q[t].y += q[t + w].y;
+          }
+        Bn = q[0].x;
+        Bv = q[0].y;
+      }
+    }
+  };
   int32_t nstop = live ? B.steps : 0;
   if constexpr (MODE == 1) {
     if (tau && live) nstop = tau[p];
   }
-  float* zrow = s_z + pl * (DMAX + 1);
+  const bool scores = MODE == 1 && tau == nullptr;
   for (int32_t n = 0; n < B.steps; ++n) {
-    float z1[A], u[A];
+    Draw dr[A];
 #pragma unroll
     for (int j = 0; j < A; ++j) {
-      const int i = i0 + j;
-      z1[j] = 0.0f;
-      u[j] = 0.5f;
-      if (i < d) {
-        const Words w = philox4x32_10((uint32_t)n, p, B.stream, (uint32_t)i, B.seed_lo, B.seed_hi);
-        float z2;
-        box_muller(u01(w.w0), u01(w.w1), z1[j], z2);
-        u[j] = u01(w.w2);
-        zrow[i] = z2;
+      const Words w = philox4x32_10((uint32_t)n, p, B.stream, (uint32_t)(i0 + j), B.seed_lo, B.seed_hi);
+      float z2;
+      box_muller(u01(w.w0), u01(w.w1), dr[j].z1, z2);
+      dr[j].u = u01(w.w2);
+      dr[j].u2 = 0.5f;
+      if (has[j]) zrow[i0 + j] = z2;
+    }
+    wave_fence();
+    float zc[A], uj[A];
+#pragma unroll
+    for (int j = 0; j < A; ++j) {
+      zc[j] = 0.0f;
+      uj[j] = 0.0f;
+    }
+#pragma unroll
+    for (int k0 = 0; k0 < DMAX; k0 += 4) {
+      if (k0 < d) {
+        const float4 t = *reinterpret_cast<const float4*>(zrow + k0);
+        const float z[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+        for (int j = 0; j < A; ++j)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) zc[j] = __builtin_fmaf(Lr[j][k0 + k], z[k], zc[j]);
+        if constexpr (MODE == 1) {
+          if (scores)
+#pragma unroll
+            for (int j = 0; j < A; ++j)
+#pragma unroll
+              for (int k = 0; k < 4; ++k) uj[j] = __builtin_fmaf(Li[j][k0 + k], z[k], uj[j]);
+        }
       }
     }
-    __syncthreads();
-    const bool step = n < nstop;
-    float s[A];
+    if (MODE != 1 || n < nstop) {
 #pragma unroll
-    for (int j = 0; j < A; ++j) {
-      const int i = i0 + j;
-      s[j] = 0.0f;
-      if (i < d && step) {
-        float zc = 0.0f;
-        const float* Lrow = s_L + i * (i + 1) / 2;
-        for (int k = 0; k <= i; ++k) zc = __builtin_fmaf(Lrow[k], zrow[k], zc);
-        Draw dr;
-        dr.z1 = z1[j];
-        dr.z2 = zc;
-        dr.u = u[j];
-        dr.u2 = 0.5f;
+      for (int j = 0; j < A; ++j) {
+        dr[j].z2 = zc[j];
         const float vb = v[j];
-        transition<SCHEME>(s_ao[i], x[j], v[j], dr);
-        if constexpr (MODE == 1) s[j] = z2_scale<SCHEME>(s_ao[i], vb, v[j]);
-      }
-    }
-    if constexpr (MODE == 1) {
-      if (tau == nullptr && step) {
-#pragma unroll
-        for (int j = 0; j < A; ++j) {
-          const int i = i0 + j;
-          if (i < d) {
-            float uj = 0.0f;  // (L^{-T} z2)_i = sum_{k >= i} (L^{-1})_ki z2_k
-            for (int k = i; k < d; ++k) uj = __builtin_fmaf(s_Li[k * (k + 1) / 2 + i], zrow[k], uj);
-            sa[j] = __builtin_fmaf(s[j], uj, sa[j]);
-            sb[j] = __builtin_fmaf(s[j], s[j], sb[j]);
+        transition<SCHEME>(o[j], x[j], v[j], dr[j]);
+        if constexpr (MODE == 1) {
+          if (scores) {
+            const float sc = z2_scale<SCHEME>(o[j], vb, v[j]);
+            sa[j] = __builtin_fmaf(sc, uj[j], sa[j]);
+            sb[j] = __builtin_fmaf(sc, sc, sb[j]);
           }
         }
       }
     }
     if constexpr (MODE == 2) {
-      float Bn = 0.0f, Bv = 0.0f;
+      float S[A], vm[A], Bn, Bv;
 #pragma unroll
       for (int j = 0; j < A; ++j) {
-        const int i = i0 + j;
-        if (i < d) {
-          const float Si = B.wS0[i] * __builtin_amdgcn_exp2f(x[j] * 1.44269504088896340736f);
-          Bn += Si;
-          Bv = __builtin_fmaf(Si, fmaxf(v[j], 0.0f), Bv);
-        }
+        S[j] = wS0[j] * __builtin_amdgcn_exp2f(x[j] * 1.44269504088896340736f);
+        vm[j] = fmaxf(v[j], 0.0f);
       }
-#pragma unroll
-      for (int off = 1; off < LPP; off <<= 1) {
-        Bn += __shfl_xor(Bn, off, kWave);
-        Bv += __shfl_xor(Bv, off, kWave);
-      }
+      basket_sums(S, vm, Bn, Bv);
       if (sub == 0 && live) {
         o1[(size_t)n * P + p] = __builtin_amdgcn_logf(Bn * B.invB0) * 0.69314718055994530942f;
         o2[(size_t)n * P + p] = Bv * rcp(Bn);
       }
     }
-    __syncthreads();  // the step's normals are overwritten by the next
+    wave_fence();  // the step's normals and sums are overwritten by the next
   }
-  if constexpr (MODE == 0 || MODE == 1) {
-    float e[A];
-    float Bt = 0.0f;
+  if constexpr (MODE != 2) {
+    float e[A], S[A], vm[A], Bt, unused;
 #pragma unroll
     for (int j = 0; j < A; ++j) {
-      e[j] = 0.0f;
-      if (i0 + j < d) {
-        e[j] = __builtin_amdgcn_exp2f(x[j] * 1.44269504088896340736f);
-        Bt += B.wS0[i0 + j] * e[j];
-      }
+      e[j] = __builtin_amdgcn_exp2f(x[j] * 1.44269504088896340736f);
+      S[j] = wS0[j] * e[j];
+      vm[j] = 0.0f;
     }
-#pragma unroll
-    for (int off = 1; off < LPP; off <<= 1) Bt += __shfl_xor(Bt, off, kWave);
+    basket_sums(S, vm, Bt, unused);
     const bool call = B.payoff == 0 || B.payoff == 3;
-    const float h = fmaxf(call ? Bt - B.K : B.K - Bt, 0.0f);
     if constexpr (MODE == 0) {
+      const float h = fmaxf(call ? Bt - B.K : B.K - Bt, 0.0f);
       const float X = (live && sub == 0) ? B.disc * h : 0.0f;
       if (live) {
 #pragma unroll
         for (int j = 0; j < A; ++j) {
-          if (i0 + j < d) {
+          if (has[j]) {
             if (o1) o1[(size_t)p * d + i0 + j] = x[j];
             if (o2) o2[(size_t)p * d + i0 + j] = v[j];
           }
@@ -3340,16 +3419,20 @@ __global__ __launch_bounds__(256) void basket_split_kernel(const DevBasket* __re
         rows[2 * (size_t)blockIdx.x] = vals[0];
         rows[2 * (size_t)blockIdx.x + 1] = vals[1];
       }
-    } else if (live) {
-      const float dsc = __builtin_amdgcn_exp2f(-B.rdt * 1.44269504088896340736f * (float)nstop);
-      const float dh = h > 0.0f ? (call ? dsc : -dsc) : 0.0f;
-      if (sub == 0) o1[p] = dsc * h;
+    } else {
+      Bt = __shfl(Bt, pl * L, kWave);  // from the path's first lane
+      if (live) {
+        const float h = fmaxf(call ? Bt - B.K : B.K - Bt, 0.0f);
+        const float dsc = __builtin_amdgcn_exp2f(-B.rdt * 1.44269504088896340736f * (float)nstop);
+        const float dh = h > 0.0f ? (call ? dsc : -dsc) : 0.0f;
+        if (sub == 0) o1[p] = dsc * h;
 #pragma unroll
-      for (int j = 0; j < A; ++j) {
-        const int i = i0 + j;
-        if (i < d) {
-          o1[(size_t)(1 + i) * P + p] = dh * B.w[i] * e[j];
-          o1[(size_t)(1 + d + i) * P + p] = tau ? 0.0f : sa[j] / sb[j];  // 0 / 0 = NaN: no score
+        for (int j = 0; j < A; ++j) {
+          const int i = i0 + j;
+          if (has[j]) {
+            o1[(size_t)(1 + i) * P + p] = dh * B.w[i] * e[j];
+            o1[(size_t)(1 + d + i) * P + p] = tau ? 0.0f : sa[j] / sb[j];  // 0 / 0 = NaN: no score
+          }
         }
       }
     }
@@ -3422,14 +3505,11 @@ __global__ __launch_bounds__(256) void basket_moments_kernel(const DevBasket* __
 
 int basket_tier(int d) { return d <= 4 ? 4 : d <= 8 ? 8 : d <= 16 ? 16 : 32; }
 
-int basket_lanes_per_path(int d, int64_t paths, int num_cus) {
-  // one lane per path with at least 2 waves per SIMD already, or too few assets to share (5 assets
-  // over 2 lanes ran slower than one lane per path on the 25,000-path Table 1 basket); else the
-  // fewest lanes per path (4, 8, 16, and 32 for more than 16 assets) that reach 6 waves per SIMD,
-  // or the most.  On the 25,000-path Table 1 baskets of 10 / 20 / 30 assets, 4 / 8 / 16 lanes
-  // took 1.00 / 0.89 / 0.82, 2.86 / 2.47 / 2.18 and 6.19 / 5.34 / 4.76 ms (32 lanes no faster);
-  // the Greeks of 32 assets on 6,000 paths 1.66 / 1.12 / 0.81 / 0.65 ms at 4 / 8 / 16 / 32: the
-  // step's transcendental and Philox chains need the extra waves to hide their latency.
+// The order of the basket sums: 1 in asset order, else by tier / l leaves of l assets.  It follows
+// the lanes per path that a first kernel for few paths had -- 4, 8, 16, or 32 for more than 16
+// assets, the fewest reaching 6 waves per SIMD -- because American prices depend on every bit of
+// the write-out.
+static int basket_order(int d, int64_t paths, int num_cus) {
   if (d <= 8 || (paths + kWave - 1) / kWave >= 2 * 4 * (int64_t)num_cus) return 1;
   const int64_t target = 6 * 4 * (int64_t)num_cus;
   const int most = d > 16 ? 32 : 16;
@@ -3438,38 +3518,55 @@ int basket_lanes_per_path(int d, int64_t paths, int num_cus) {
   return most;
 }
 
-template <int SCHEME, int DMAX, int LPP>
-static hipError_t launch_split_t(int mode, int64_t paths, const DevBasket* bk, const DevOpt* ao, const int32_t* tau,
-                                 float* o1, float* o2, float* o3, uint32_t* zero, int64_t nzero, double* rows,
-                                 hipStream_t s) {
-  constexpr int PB = 256 / LPP;
-  const int grid = (int)((paths + PB - 1) / PB);
+BasketLayout basket_layout(int mode, int d, int64_t paths, int num_cus) {
+  BasketLayout l;
+  const int lpp = basket_order(d, paths, num_cus);
+  l.leaf = lpp > 1 ? basket_tier(d) / lpp : 0;
+  // The wave kernel up to this many waves per SIMD at one path per lane, where it and one path per
+  // lane measured the same.  us per call, one path per lane / wave: 8 assets x 252 steps, 131,072
+  // paths: Greeks 1,362 / 786; 262,144 x 63: 550 / 447, write-out and induction 796 / 771; 2^20 x 20:
+  // 645 / 622 and 734 / 780.  The write-out sums the basket every step, in asset order from 2 waves
+  // per SIMD on, one lane per path at work: 20 assets, 131,072 paths x 50 965 / 1,023, 262,144 x 30
+  // 855 / 1,091.  32 assets, 262,144 x 10: price 471 / 507, Greeks 1,259 / 1,122.
+  const int64_t limit = mode == 2 ? (d <= 8 ? 8 : 2) : mode == 1 ? 8 : (d <= 16 ? 8 : 4);
+  if (d >= 3 && (paths + kWave - 1) / kWave < limit * 4 * (int64_t)num_cus) l.per_lane = d <= 8 || l.leaf == 1 ? 1 : 2;
+  int per_block = 256;
+  if (l.per_lane) per_block = 4 * (kWave / ((d + l.per_lane - 1) / l.per_lane));
+  l.blocks = (int)((paths + per_block - 1) / per_block);
+  return l;
+}
+
+template <int SCHEME, int DMAX, int A, int LEAFA>
+static hipError_t launch_wave_t(int mode, int grid, const DevBasket* bk, const DevOpt* ao, const int32_t* tau,
+                                float* o1, float* o2, float* o3, uint32_t* zero, int64_t nzero, double* rows,
+                                hipStream_t s) {
   if (mode == 0)
-    hipLaunchKernelGGL((basket_split_kernel<SCHEME, DMAX, LPP, 0>), dim3(grid), dim3(256), 0, s, bk, ao, tau, o1, o2,
-                       o3, zero, nzero, rows);
+    hipLaunchKernelGGL((basket_wave_kernel<SCHEME, DMAX, A, LEAFA, 0>), dim3(grid), dim3(256), 0, s, bk, ao, tau, o1,
+                       o2, o3, zero, nzero, rows);
   else if (mode == 1)
-    hipLaunchKernelGGL((basket_split_kernel<SCHEME, DMAX, LPP, 1>), dim3(grid), dim3(256), 0, s, bk, ao, tau, o1, o2,
-                       o3, zero, nzero, rows);
+    hipLaunchKernelGGL((basket_wave_kernel<SCHEME, DMAX, A, LEAFA, 1>), dim3(grid), dim3(256), 0, s, bk, ao, tau, o1,
+                       o2, o3, zero, nzero, rows);
+  else if constexpr (DMAX == 8 || LEAFA != 0)
+    hipLaunchKernelGGL((basket_wave_kernel<SCHEME, DMAX, A, LEAFA, 2>), dim3(grid), dim3(256), 0, s, bk, ao, tau, o1,
+                       o2, o3, zero, nzero, rows);
   else
-    hipLaunchKernelGGL((basket_split_kernel<SCHEME, DMAX, LPP, 2>), dim3(grid), dim3(256), 0, s, bk, ao, tau, o1, o2,
-                       o3, zero, nzero, rows);
+    return hipErrorInvalidValue;  // in asset order, more than 8 assets are written out one path per lane
   return hipGetLastError();
 }
 
 template <int SCHEME>
-static hipError_t launch_split_s(int mode, int d, int lpp, int64_t paths, const DevBasket* bk, const DevOpt* ao,
-                                 const int32_t* tau, float* o1, float* o2, float* o3, uint32_t* zero, int64_t nzero,
-                                 double* rows, hipStream_t s) {
-  if (d <= 16) {
-    if (lpp > 16) return hipErrorInvalidValue;
-    if (lpp == 4) return launch_split_t<SCHEME, 16, 4>(mode, paths, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
-    if (lpp == 8) return launch_split_t<SCHEME, 16, 8>(mode, paths, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
-    return launch_split_t<SCHEME, 16, 16>(mode, paths, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
-  }
-  if (lpp == 4) return launch_split_t<SCHEME, 32, 4>(mode, paths, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
-  if (lpp == 8) return launch_split_t<SCHEME, 32, 8>(mode, paths, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
-  if (lpp == 16) return launch_split_t<SCHEME, 32, 16>(mode, paths, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
-  return launch_split_t<SCHEME, 32, 32>(mode, paths, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
+static hipError_t launch_wave_s(int mode, int d, const BasketLayout& l, const DevBasket* bk, const DevOpt* ao,
+                                const int32_t* tau, float* o1, float* o2, float* o3, uint32_t* zero, int64_t nzero,
+                                double* rows, hipStream_t s) {
+  const int g = l.blocks;
+#define SIMR_WAVE(D, A, LEAF)                                                                                  \
+  if (basket_tier(d) <= D && (D > 8 || l.leaf == 0) && l.per_lane == A && l.leaf == LEAF)                      \
+    return launch_wave_t<SCHEME, D, A, LEAF>(mode, g, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
+  SIMR_WAVE(8, 1, 0)
+  SIMR_WAVE(16, 1, 1) SIMR_WAVE(16, 2, 2) SIMR_WAVE(16, 2, 4) SIMR_WAVE(16, 2, 0)
+  SIMR_WAVE(32, 1, 1) SIMR_WAVE(32, 2, 2) SIMR_WAVE(32, 2, 4) SIMR_WAVE(32, 2, 8) SIMR_WAVE(32, 2, 0)
+#undef SIMR_WAVE
+  return hipErrorInvalidValue;
 }
 
 template <int SCHEME, int DMAX>
@@ -3560,20 +3657,20 @@ static hipError_t launch_basket_s(int mode, int d, int grid, const DevBasket* bk
   }
 }
 
-hipError_t launch_basket_paths(int scheme, int mode, int d, int64_t paths, int lpp, const DevBasket* bk,
+hipError_t launch_basket_paths(int scheme, int mode, int d, int64_t paths, const BasketLayout& l, const DevBasket* bk,
                                const DevOpt* ao, const int32_t* tau, float* o1, float* o2, float* o3, uint32_t* zero,
                                int64_t nzero, double* rows, hipStream_t s) {
   if (d < 1 || d > kMaxAssets || mode < 0 || mode > 2) return hipErrorInvalidValue;
-  if (lpp > 1) {
-    if (d <= 8 || (lpp != 4 && lpp != 8 && lpp != 16 && lpp != 32)) return hipErrorInvalidValue;
+  if (l.per_lane) {
     switch (scheme) {
-      case 0: return launch_split_s<0>(mode, d, lpp, paths, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
-      case 1: return launch_split_s<1>(mode, d, lpp, paths, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
-      case 2: return launch_split_s<2>(mode, d, lpp, paths, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
-      case 3: return launch_split_s<3>(mode, d, lpp, paths, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
+      case 0: return launch_wave_s<0>(mode, d, l, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
+      case 1: return launch_wave_s<1>(mode, d, l, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
+      case 2: return launch_wave_s<2>(mode, d, l, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
+      case 3: return launch_wave_s<3>(mode, d, l, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);
       default: return hipErrorInvalidValue;
     }
   }
+  if (l.leaf) return hipErrorInvalidValue;
   const int grid = (int)((paths + 255) / 256);
   switch (scheme) {
     case 0: return launch_basket_s<0>(mode, d, grid, bk, ao, tau, o1, o2, o3, zero, nzero, rows, s);

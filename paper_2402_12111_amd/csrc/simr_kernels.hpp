@@ -192,12 +192,14 @@ struct DevBasket {
 
 // The smallest compiled asset tile (4, 8, 16, 32) holding d assets.
 int basket_tier(int d);
-// Lanes per path of the basket kernels: 1 (one path per lane), or 4 (the split kernel) for more
-// than 8 assets and fewer than two waves per SIMD at one path per lane.
-int basket_lanes_per_path(int d, int64_t paths, int num_cus);
-// mode 0 price, 1 Greeks records, 2 Longstaff-Schwartz write-out (see basket_path_kernel);
-// lpp from basket_lanes_per_path (rows: 2 doubles per block of 256 / lpp paths).
-hipError_t launch_basket_paths(int scheme, int mode, int d, int64_t paths, int lpp, const DevBasket* bk,
+// How a basket's paths are laid out on lanes.  leaf fixes the order of the basket sums: the assets one
+// after another (0), or in leaves of `leaf` assets, then pairwise.  per_lane: 0, one path per lane
+// (leaf = 0); or the assets per lane of the wave kernel.  blocks: of 256 threads.
+struct BasketLayout { int leaf = 0, per_lane = 0, blocks = 0; };
+BasketLayout basket_layout(int mode, int d, int64_t paths, int num_cus);
+// mode 0 price, 1 Greeks records, 2 Longstaff-Schwartz write-out (see basket_path_kernel); rows: 2
+// doubles per block of the layout.
+hipError_t launch_basket_paths(int scheme, int mode, int d, int64_t paths, const BasketLayout& l, const DevBasket* bk,
                                const DevOpt* ao, const int32_t* tau, float* o1, float* o2, float* o3, uint32_t* zero,
                                int64_t nzero, double* rows, hipStream_t s);
 // Risk records of a basket of d <= kRiskMaxAssets assets (QE, full-truncation Euler or truncated
