@@ -445,6 +445,59 @@ __global__ __launch_bounds__(BLOCK) void lsm_step_kernel(DevOpt o, int32_t n, co
   }
 }
 
+// v of lane l ^ 4, within each row of 16.
+__device__ __forceinline__ float lane_xor4(float v) {
+  const int x = __float_as_int(v);
+  int t = __builtin_amdgcn_update_dpp(0, x, 0x104, 0xF, 0x5, false);  // row_shl:4 into banks 0 and 2
+  t = __builtin_amdgcn_update_dpp(t, x, 0x114, 0xF, 0xA, false);      // row_shr:4 into banks 1 and 3
+  return __int_as_float(t);
+}
+
+// The sums of NV values over each 16-lane row, value q left in the lanes with q in their low bits
+// (lane l of a row holds value l for l < NV): each step adds a lane's partner, l ^ 1, l ^ 2, l ^ 4,
+// l ^ 8, for half of the values only -- a lane keeps one value of a pair and hands the other over --
+// so 6 values take 18 operations where row_sum16 of each takes 24, and one LDS store replaces 6.
+// The additions pair the same lanes in the same order as row_sum16, so the sums are the same bits.
+// One step: lo and hi hold two values; a lane with `upper` keeps hi and gives lo.  (The empty statement
+// keeps the pair in registers of their own: of elements of an array the compiler makes one indexed
+// look-up, a chain of compares.)
+template <class Partner>
+__device__ __forceinline__ float scatter_pair(float lo, float hi, bool upper, Partner partner) {
+  asm("" : "+v"(lo), "+v"(hi));
+  const float keep = upper ? hi : lo, give = upper ? lo : hi;
+  return keep + partner(give);
+}
+
+template <int NV>
+__device__ __forceinline__ float row_sums_scattered(const float (&v)[NV]) {
+  static_assert(NV <= 16, "a value per lane of the row");
+  const int lane = threadIdx.x & (kWave - 1);
+  constexpr int N1 = (NV + 1) / 2, N2 = (N1 + 1) / 2, N3 = (N2 + 1) / 2;
+  static_assert(N3 <= 2, "at most two values before the last step");
+  const auto x1 = [](float t) { return dpp_term<0xB1, 0xF>(t); };  // quad_perm [1,0,3,2]
+  const auto x2 = [](float t) { return dpp_term<0x4E, 0xF>(t); };  // quad_perm [2,3,0,1]
+  const auto x4 = [](float t) { return lane_xor4(t); };
+  const auto x8 = [](float t) { return dpp_term<0x128, 0xF>(t); };  // row_ror:8
+  float r1[N1], r2[N2], r3[N3];
+#pragma unroll
+  for (int i = 0; i < N1; ++i) {
+    if (2 * i + 1 < NV) r1[i] = scatter_pair(v[2 * i], v[2 * i + 1 < NV ? 2 * i + 1 : 0], lane & 1, x1);
+    else r1[i] = v[2 * i] + x1(v[2 * i]);
+  }
+#pragma unroll
+  for (int i = 0; i < N2; ++i) {
+    if (2 * i + 1 < N1) r2[i] = scatter_pair(r1[2 * i], r1[2 * i + 1 < N1 ? 2 * i + 1 : 0], lane & 2, x2);
+    else r2[i] = r1[2 * i] + x2(r1[2 * i]);
+  }
+#pragma unroll
+  for (int i = 0; i < N3; ++i) {
+    if (2 * i + 1 < N2) r3[i] = scatter_pair(r2[2 * i], r2[2 * i + 1 < N2 ? 2 * i + 1 : 0], lane & 4, x4);
+    else r3[i] = r2[2 * i] + x4(r2[2 * i]);
+  }
+  if constexpr (N3 == 2) return scatter_pair(r3[0], r3[1], lane & 8, x8);
+  else return r3[0] + x8(r3[0]);
+}
+
 // ---------------------------------------------------------------------------------------------
 // The Gram matrices of all dates, before the backward induction.  The in-the-money set and the
 // basis at date n depend only on the path states at n, so sum phi phi^T (and the count) of every
@@ -482,8 +535,8 @@ __device__ __forceinline__ void gram_block(const DevOpt& o, int32_t n, uint32_t 
                                            int32_t per_lane, float* __restrict__ gram) {
   constexpr int kGramSums = LsmLayout<NB>::kSums;
   constexpr int kGramRow = LsmLayout<NB>::kRow;
-  __shared__ float s_red[kGramSums * (BLOCK / kWave)];
   const size_t P = (size_t)o.paths;
+  const float sign = is_call(o.payoff) ? 1.0f : -1.0f;
   float acc[kGramSums];
 #pragma unroll
   for (int i = 0; i < kGramSums; ++i) acc[i] = 0.0f;
@@ -503,12 +556,12 @@ __device__ __forceinline__ void gram_block(const DevOpt& o, int32_t n, uint32_t 
   }
 #pragma unroll
   for (int j = 0; j < kGramMaxPerLane; ++j) {
-    float S = asset(o, xb[j]);
+    float d = asset(o, xb[j]) - o.K;
     float c = lsm_c(o, vb[j]);
-    asm volatile("" : "+v"(S), "+v"(c));  // formed here, in path order, not inside the branch
-    if (ok[j] && intrinsic(o, S) > 0.0f) {
+    asm volatile("" : "+v"(d), "+v"(c));  // formed here, in path order, not inside the branch
+    if (ok[j] && sign * d > 0.0f) {  // in the money: S - K or K - S is positive
+      const float a = d * o.invK;    // lsm_a
       if constexpr (NB == 6) {
-        const float a = lsm_a(o, S);
         const float a2 = a * a, ac = a * c, c2 = c * c;
         acc[gram_moment(0, 0)] += 1.0f;
         acc[gram_moment(1, 0)] += a;
@@ -527,7 +580,7 @@ __device__ __forceinline__ void gram_block(const DevOpt& o, int32_t n, uint32_t 
         acc[gram_moment(0, 4)] = __builtin_fmaf(c2, c2, acc[gram_moment(0, 4)]);
       } else {
         float phi[NB];
-        lsm_basis_nb_ac<NB>(lsm_a(o, S), c, phi);
+        lsm_basis_nb_ac<NB>(a, c, phi);
         // entry (0, 0) is phi_0^2 = 1 per path, the in-the-money count: summed once, below
         int q = 1;
 #pragma unroll
@@ -539,11 +592,34 @@ __device__ __forceinline__ void gram_block(const DevOpt& o, int32_t n, uint32_t 
     }
   }
   if constexpr (NB != 6) acc[0] = acc[kGramSums - 1];
-  block_sum<BLOCK, kGramSums, float>(acc, s_red);
-  if (threadIdx.x == 0) {
-    float* row = gram + ((size_t)n * chunks + chunk) * kGramRow;
+  float* row = gram + ((size_t)n * chunks + chunk) * kGramRow;
+  if constexpr (NB == 6) {
+    // The sums block_sum forms, in fewer instructions (about 45 for the 15 values of a wave, where
+    // a DPP tree for each took 105): the 16-lane rows leave value q in lane q, the 16 row sums of a
+    // value pass through LDS, and one lane per value adds them pairwise, the rows of a wave first.
+    // Below 2^20 paths the pass is bound by issue, not by HBM: 30 options of 25,000 paths x 503 dates
+    // 866 -> 586 us (5.1 TB/s of the 5.2 a copy reaches), 131,072 x 251 43 -> 39.
+    constexpr int R = BLOCK / 16;
+    static_assert(R == 16 && kGramSums <= 16, "16 rows of at most 16 values");
+    __shared__ __align__(16) float s_row[kGramSums * R];
+    const float sum = row_sums_scattered<kGramSums>(acc);
+    const int q = threadIdx.x & 15;
+    if (q < kGramSums) s_row[q * R + (threadIdx.x >> 4)] = sum;
+    __syncthreads();
+    if (threadIdx.x < kGramSums) {
+      const float4* r4 = reinterpret_cast<const float4*>(s_row + threadIdx.x * R);
+      float w[4];  // the waves' sums
 #pragma unroll
-    for (int i = 0; i < kGramSums; ++i) row[i] = acc[i];
+      for (int k = 0; k < 4; ++k) w[k] = (r4[k].x + r4[k].y) + (r4[k].z + r4[k].w);
+      row[threadIdx.x] = (w[0] + w[1]) + (w[2] + w[3]);
+    }
+  } else {
+    __shared__ float s_red[kGramSums * (BLOCK / kWave)];
+    block_sum<BLOCK, kGramSums, float>(acc, s_red);
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int i = 0; i < kGramSums; ++i) row[i] = acc[i];
+    }
   }
 }
 
@@ -588,18 +664,23 @@ __device__ __forceinline__ double readlane_d(double x, int l) {
 // columns, M = P^T (L L^T)^{-1} P (36), rank, count, valid.
 constexpr int kFactorThreads = 256;
 
+// NW: the waves that sum a date's rows, the whole block or (kFactorRows rows or fewer) each wave a date
+// of its own: the other waves' partials would be 0.
+constexpr int kFactorRows = 64;
+
+template <int NW>
 __device__ __forceinline__ void factor_block(int32_t n, int32_t chunks, double rdt, const float* __restrict__ gram,
                                              double* __restrict__ fac, int32_t* __restrict__ flags) {
-  constexpr int W = kFactorThreads / kWave;
+  constexpr int W = NW;
   static_assert(kGramRow % 4 == 0 && kGramSums <= kGramRow, "rows of whole 16-byte words");
   __shared__ double s_part[kGramSums * W];
   const int lane = threadIdx.x & (kWave - 1);
-  const int wid = threadIdx.x / kWave;
+  const int wid = NW == 1 ? 0 : threadIdx.x / kWave;
   double part[kGramSums];
 #pragma unroll
   for (int e = 0; e < kGramSums; ++e) part[e] = 0.0;
   const float* rows = gram + (size_t)n * chunks * kGramRow;
-  for (int c = threadIdx.x; c < chunks; c += kFactorThreads) {
+  for (int c = NW == 1 ? lane : threadIdx.x; c < chunks; c += NW * kWave) {
     const float4* r4 = reinterpret_cast<const float4*>(rows + (size_t)c * kGramRow);
     float q[kGramRow];
 #pragma unroll
@@ -617,16 +698,21 @@ __device__ __forceinline__ void factor_block(int32_t n, int32_t chunks, double r
   for (int off = 32; off > 0; off >>= 1)  // each step on every entry before the next
 #pragma unroll
     for (int e = 0; e < kGramSums; ++e) part[e] += __shfl_xor(part[e], off, kWave);
-  if (lane == 0) {
-#pragma unroll
-    for (int e = 0; e < kGramSums; ++e) s_part[e * W + wid] = part[e];
-  }
-  __syncthreads();
-  if (wid != 0) return;
   double sum = 0.0;
-  if (lane < kGramSums) {
-    sum = s_part[lane * W];
-    for (int w = 1; w < W; ++w) sum += s_part[lane * W + w];
+  if constexpr (NW > 1) {
+    if (lane == 0) {
+#pragma unroll
+      for (int e = 0; e < kGramSums; ++e) s_part[e * W + wid] = part[e];
+    }
+    __syncthreads();
+    if (wid != 0) return;
+    if (lane < kGramSums) {
+      sum = s_part[lane * W];
+      for (int w = 1; w < W; ++w) sum += s_part[lane * W + w];
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < kGramSums; ++e) sum = lane == e ? part[e] : sum;
   }
   const double count = readlane_d(sum, gram_moment(0, 0));
   double* rec = fac + (size_t)n * kFacRec;
@@ -675,53 +761,31 @@ __device__ __forceinline__ void factor_block(int32_t n, int32_t chunks, double r
     if (in && i > r && j > r) a -= lir * ljr;
   }
   // M = P^T (L L^T)^{-1} P on the kept columns (zero rows/columns for dropped ones), so that
-  // the induction's solve is beta = M y.  Lane 0 inverts the triangular factor: W = L^{-1},
-  // (L L^T)^{-1} = W^T W.
+  // the induction's solve is beta = M y.  (L L^T)^{-1} = W^T W with W = L^{-1}: lane c < 6 forms
+  // column c of W (L W[:, c] = e_c), lane 6 i + j entry (i, j) of M.  (One lane forming all of both
+  // made this the longest part of a date: 331 us for the 15,090 dates of 30 options, 51 so.)
   double Lr[6][6];
 #pragma unroll
   for (int r = 0; r < 6; ++r)
 #pragma unroll
     for (int c = 0; c < 6; ++c) Lr[r][c] = (c <= r) ? readlane_d(a, r * 6 + c) : 0.0;
-  int pr[6];
+  double Wc[6];  // W[r][lane]
 #pragma unroll
-  for (int c = 0; c < 6; ++c) pr[c] = __builtin_amdgcn_readlane(perm, c);
+  for (int r = 0; r < 6; ++r) {
+    double t = 0.0;
+#pragma unroll
+    for (int q = 0; q < r; ++q)
+      if (q >= lane) t += Lr[r][q] * Wc[q];
+    const bool kept = r < rank && lane < rank && r >= lane;
+    const double num = r == lane ? 1.0 : -t;
+    Wc[r] = kept ? num / Lr[r][r] : 0.0;
+  }
+  double m = 0.0;
+#pragma unroll
+  for (int q = 0; q < 6; ++q) m += __shfl(Wc[q], in ? i : 0, kWave) * __shfl(Wc[q], in ? j : 0, kWave);
+  const int pi = __shfl(perm, in ? i : 0, kWave), pj = __shfl(perm, in ? j : 0, kWave);
+  if (in) rec[pi * 6 + pj] = i < rank && j < rank ? m : 0.0;
   if (lane == 0) {
-    double W[6][6];
-#pragma unroll
-    for (int r = 0; r < 6; ++r)
-#pragma unroll
-      for (int c = 0; c < 6; ++c) W[r][c] = 0.0;
-#pragma unroll
-    for (int c = 0; c < 6; ++c) {  // column c of W: L W[:, c] = e_c
-      if (c < rank) {
-        W[c][c] = 1.0 / Lr[c][c];
-#pragma unroll
-        for (int r = c + 1; r < 6; ++r) {
-          if (r < rank) {
-            double t = 0.0;
-#pragma unroll
-            for (int q = c; q < r; ++q) t += Lr[r][q] * W[q][c];
-            W[r][c] = -t / Lr[r][r];
-          }
-        }
-      }
-    }
-    double M[6][6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-      for (int j = 0; j < 6; ++j) {
-        double t = 0.0;
-#pragma unroll
-        for (int q = 0; q < 6; ++q) t += W[q][i] * W[q][j];
-        M[i][j] = t;
-      }
-    for (int i = 0; i < 36; ++i) rec[i] = 0.0;
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-      for (int j = 0; j < 6; ++j)
-        if (i < rank && j < rank) rec[pr[i] * 6 + pr[j]] = M[i][j];
     rec[48] = (double)rank;
     rec[49] = count;
     rec[50] = 1.0;
@@ -734,16 +798,28 @@ __global__ __launch_bounds__(kFactorThreads) void lsm_factor_kernel(int32_t chun
                                                                     const float* __restrict__ gram,
                                                                     double* __restrict__ fac,
                                                                     int32_t* __restrict__ flags) {
-  factor_block((int32_t)blockIdx.x + 1, chunks, rdt, gram, fac, flags);
+  factor_block<kFactorThreads / kWave>((int32_t)blockIdx.x + 1, chunks, rdt, gram, fac, flags);
 }
 
-// The factorisations of every date of several options in one launch.
+// The same for at most kFactorRows rows a date: a date per wave.
+__global__ __launch_bounds__(kFactorThreads) void lsm_factor_wave_kernel(int32_t dates, int32_t chunks, double rdt,
+                                                                         const float* __restrict__ gram,
+                                                                         double* __restrict__ fac,
+                                                                         int32_t* __restrict__ flags) {
+  const int32_t n = (int32_t)(blockIdx.x * (kFactorThreads / kWave) + threadIdx.x / kWave) + 1;
+  if (n > dates) return;
+  factor_block<1>(n, chunks, rdt, gram, fac, flags);
+}
+
+// The factorisations of every date of several options (of at most kFactorRows rows a date) in one
+// launch, a date per wave.
 __global__ __launch_bounds__(kFactorThreads) void factor_tasks_kernel(const LsmTask* __restrict__ tasks,
                                                                       int32_t ntasks) {
-  const int32_t t = task_of_block<&LsmTask::fac0, &LsmTask::facn>(tasks, ntasks, blockIdx.x);
+  const uint32_t u = blockIdx.x * (kFactorThreads / kWave) + threadIdx.x / kWave;
+  const int32_t t = task_of_block<&LsmTask::fac0, &LsmTask::facn>(tasks, ntasks, u);
   if (t < 0) return;
   const LsmTask& T = tasks[t];
-  factor_block((int32_t)(blockIdx.x - (uint32_t)T.fac0) + 1, T.chunks, T.rdt, T.gram, T.fac, T.flags);
+  factor_block<1>((int32_t)(u - (uint32_t)T.fac0) + 1, T.chunks, T.rdt, T.gram, T.fac, T.flags);
 }
 
 // The same record for a basis of NB functions (NB = 10): the lanes sum the chunk rows as above,
@@ -999,59 +1075,6 @@ __device__ __forceinline__ float row_sum16(float x) {
   x += dpp_term<0x141, 0xF>(x);  // row_half_mirror
   x += dpp_term<0x140, 0xF>(x);  // row_mirror
   return x;
-}
-
-// v of lane l ^ 4, within each row of 16.
-__device__ __forceinline__ float lane_xor4(float v) {
-  const int x = __float_as_int(v);
-  int t = __builtin_amdgcn_update_dpp(0, x, 0x104, 0xF, 0x5, false);  // row_shl:4 into banks 0 and 2
-  t = __builtin_amdgcn_update_dpp(t, x, 0x114, 0xF, 0xA, false);      // row_shr:4 into banks 1 and 3
-  return __int_as_float(t);
-}
-
-// The sums of NV values over each 16-lane row, value q left in the lanes with q in their low bits
-// (lane l of a row holds value l for l < NV): each step adds a lane's partner, l ^ 1, l ^ 2, l ^ 4,
-// l ^ 8, for half of the values only -- a lane keeps one value of a pair and hands the other over --
-// so 6 values take 18 operations where row_sum16 of each takes 24, and one LDS store replaces 6.
-// The additions pair the same lanes in the same order as row_sum16, so the sums are the same bits.
-// One step: lo and hi hold two values; a lane with `upper` keeps hi and gives lo.  (The empty statement
-// keeps the pair in registers of their own: of elements of an array the compiler makes one indexed
-// look-up, a chain of compares.)
-template <class Partner>
-__device__ __forceinline__ float scatter_pair(float lo, float hi, bool upper, Partner partner) {
-  asm("" : "+v"(lo), "+v"(hi));
-  const float keep = upper ? hi : lo, give = upper ? lo : hi;
-  return keep + partner(give);
-}
-
-template <int NV>
-__device__ __forceinline__ float row_sums_scattered(const float (&v)[NV]) {
-  static_assert(NV <= 16, "a value per lane of the row");
-  const int lane = threadIdx.x & (kWave - 1);
-  constexpr int N1 = (NV + 1) / 2, N2 = (N1 + 1) / 2, N3 = (N2 + 1) / 2;
-  static_assert(N3 <= 2, "at most two values before the last step");
-  const auto x1 = [](float t) { return dpp_term<0xB1, 0xF>(t); };  // quad_perm [1,0,3,2]
-  const auto x2 = [](float t) { return dpp_term<0x4E, 0xF>(t); };  // quad_perm [2,3,0,1]
-  const auto x4 = [](float t) { return lane_xor4(t); };
-  const auto x8 = [](float t) { return dpp_term<0x128, 0xF>(t); };  // row_ror:8
-  float r1[N1], r2[N2], r3[N3];
-#pragma unroll
-  for (int i = 0; i < N1; ++i) {
-    if (2 * i + 1 < NV) r1[i] = scatter_pair(v[2 * i], v[2 * i + 1 < NV ? 2 * i + 1 : 0], lane & 1, x1);
-    else r1[i] = v[2 * i] + x1(v[2 * i]);
-  }
-#pragma unroll
-  for (int i = 0; i < N2; ++i) {
-    if (2 * i + 1 < N1) r2[i] = scatter_pair(r1[2 * i], r1[2 * i + 1 < N1 ? 2 * i + 1 : 0], lane & 2, x2);
-    else r2[i] = r1[2 * i] + x2(r1[2 * i]);
-  }
-#pragma unroll
-  for (int i = 0; i < N3; ++i) {
-    if (2 * i + 1 < N2) r3[i] = scatter_pair(r2[2 * i], r2[2 * i + 1 < N2 ? 2 * i + 1 : 0], lane & 4, x4);
-    else r3[i] = r2[2 * i] + x4(r2[2 * i]);
-  }
-  if constexpr (N3 == 2) return scatter_pair(r3[0], r3[1], lane & 8, x8);
-  else return r3[0] + x8(r3[0]);
 }
 
 // The fold of 64 row partials of NV values (s[q 64 + r]) as wave_sum adds them, a lane starting with
@@ -2425,9 +2448,10 @@ hipError_t launch_gram_tasks(const LsmTask* tasks, int ntasks, int grid, hipStre
   return hipGetLastError();
 }
 
-hipError_t launch_factor_tasks(const LsmTask* tasks, int ntasks, int grid, hipStream_t s) {
-  if (grid < 1) return hipSuccess;
-  hipLaunchKernelGGL(factor_tasks_kernel, dim3(grid), dim3(kFactorThreads), 0, s, tasks, ntasks);
+hipError_t launch_factor_tasks(const LsmTask* tasks, int ntasks, int dates, hipStream_t s) {
+  if (dates < 1) return hipSuccess;
+  constexpr int per_block = kFactorThreads / kWave;
+  hipLaunchKernelGGL(factor_tasks_kernel, dim3((dates + per_block - 1) / per_block), dim3(kFactorThreads), 0, s, tasks, ntasks);
   return hipGetLastError();
 }
 
@@ -2651,7 +2675,11 @@ hipError_t launch_lsm_factor(const DevOpt& o, double rdt, const float* gram, dou
                              hipStream_t s, int nb) {
   if (o.steps < 2) return hipSuccess;
   const int chunks = lsm_gram_chunks(o.paths);
-  if (nb == 6) {
+  constexpr int per_block = kFactorThreads / kWave;
+  if (nb == 6 && chunks <= kFactorRows) {
+    hipLaunchKernelGGL(lsm_factor_wave_kernel, dim3((o.steps - 1 + per_block - 1) / per_block), dim3(kFactorThreads), 0,
+                       s, o.steps - 1, chunks, rdt, gram, fac, flags);
+  } else if (nb == 6) {
     hipLaunchKernelGGL(lsm_factor_kernel, dim3(o.steps - 1), dim3(kFactorThreads), 0, s, chunks, rdt, gram, fac,
                        flags);
   } else if (nb == 10) {

@@ -114,11 +114,12 @@ hipError_t launch_lsm_gram(const DevOpt& o, const float* xs, const float* vs, fl
 hipError_t launch_lsm_factor(const DevOpt& o, double rdt, const float* gram, double* fac, int32_t* flags,
                              hipStream_t s, int nb = 6);
 // The same three passes for every task of a device table in one launch each (grid: the sum of
-// the tasks' spilln, gramn or facn); the spill also zeroes zero[0, nzero).
+// the tasks' spilln or gramn; dates: of their facn); the spill also zeroes zero[0, nzero).
 hipError_t launch_spill_tasks(int scheme, const LsmTask* tasks, int ntasks, int grid, uint32_t* zero, int64_t nzero,
                               hipStream_t s);
 hipError_t launch_gram_tasks(const LsmTask* tasks, int ntasks, int grid, hipStream_t s);
-hipError_t launch_factor_tasks(const LsmTask* tasks, int ntasks, int grid, hipStream_t s);
+// (every option of at most 2^18 paths, so a date's Gram rows are at most 64)
+hipError_t launch_factor_tasks(const LsmTask* tasks, int ntasks, int dates, hipStream_t s);
 // tasks: device array, sorted by block0, block0 relative to this launch.
 hipError_t launch_lsm_coop(const LsmTask* tasks, int ntasks, const LsmLaunchSet& ls, int32_t* status, hipStream_t s,
                            int nb = 6);
