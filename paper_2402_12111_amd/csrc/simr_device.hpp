@@ -114,6 +114,7 @@ __device__ __forceinline__ void box_muller(float u0, float u1, float& z1, float&
 
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
+__device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
 
 // The variates of transition n of path p (u2, from word 3, is drawn by the Broadie-Kaya scheme
 // only).
