@@ -783,12 +783,35 @@ simr_status autotune(simr_ctx* c, int scheme, const TuneBufs& tb, hipStream_t s)
   return SIMR_OK;
 }
 
+// One option of at most this many paths is priced by price_solo_kernel: from two waves of paths per
+// SIMD on, the drawing waves no longer find idle issue slots, and LDS is extra work.  Measured (us per call,
+// batch kernel with its upload, queue and sums / this): 8,192 paths x 64 steps 50.5 / 37.1, x 252
+// 93.4 / 65.0; 65,536 x 252 95.5 / 81.7; 131,072 x 252 122.6 / 114.4; 196,608 x 252 152.6 / 157.4;
+// 2^19 x 252 303 / 336.
+constexpr int64_t kSoloPaths = 1 << 17;
+
+bool solo(int scheme, int64_t paths) { return scheme != SIMR_SCHEME_BK && paths <= kSoloPaths; }
+
+// Prices `o` (constants `d`, tile as tuned) and leaves {sum X, sum X^2} in `host` once the stream
+// is synchronised; `sums` holds two doubles per wave of a tile, at most kSoloPaths / 64 + 4 waves.
+simr_status enqueue_solo(simr_ctx* c, int scheme, const DevOpt& d, int block, int ppl, double* sums, double* results,
+                         double* host, hipStream_t s) {
+  {
+    Prof pf(c, SIMR_PROF_PRICE, s);
+    SIMR_HIP(launch_price_solo(scheme, d, block, ppl, sums, s));
+  }
+  SIMR_HIP(launch_solo_sum(d, block, sums, results, s));
+  SIMR_HIP(hipMemcpyAsync(host, results, sizeof(double) * 2, hipMemcpyDeviceToHost, s));
+  return SIMR_OK;
+}
+
 // ---------------------------------------------------------------------------------------------
 // European batch: upload the option table, reset the queue, persistent launch, finalize,
 // download -- captured once per shape into a hipGraph and replayed.
 // ---------------------------------------------------------------------------------------------
 simr_status run_euro_batch(simr_ctx* c, int scheme, const simr_option* opts, const std::vector<int64_t>& idx,
-                           const BatchBufs& b, int64_t total_tiles, simr_result* out, hipStream_t s) {
+                           const BatchBufs& b, const TuneBufs& tb, int64_t total_tiles, simr_result* out,
+                           hipStream_t s) {
   const int64_t m = (int64_t)idx.size();
   if (m == 0) return SIMR_OK;
   const int block = c->tile_block[scheme], ppl = c->tile_ppl[scheme];
@@ -847,7 +870,11 @@ simr_status run_euro_batch(simr_ctx* c, int scheme, const simr_option* opts, con
     return SIMR_OK;
   };
 
-  if (s != nullptr && !c->prof_on) {
+  const bool captured = s != nullptr && !c->prof_on;
+  if (!captured && m == 1 && solo(scheme, opts[idx[0]].paths)) {
+    // (a captured launch would keep the constants of the option it was captured with)
+    if ((st = enqueue_solo(c, scheme, dopt[0], block, ppl, tb.partials, b.results, res_host, s)) != SIMR_OK) return st;
+  } else if (captured) {
     auto key = std::make_tuple((uintptr_t)b.upload, (uintptr_t)c->pinned, (int)m, (int)nunits, block, ppl, scheme,
                                L.grid, (uintptr_t)s);
     auto it = c->graphs.find(key);
@@ -1339,7 +1366,7 @@ simr_status simr_price_batch(simr_ctx* ctx, const simr_option* opts, int64_t n, 
   const int tile = (ctx->tile_block[scheme] ? ctx->tile_block[scheme] * ctx->tile_ppl[scheme] : kMinTilePaths);
   BatchPlan pl = plan_batch(opts, n, tile);
   BatchBufs bb = carve_batch(cv, (int64_t)pl.euro.size(), pl.total_tiles);
-  if ((st = run_euro_batch(ctx, scheme, opts, pl.euro, bb, pl.total_tiles, res.data(), s)) != SIMR_OK) return st;
+  if ((st = run_euro_batch(ctx, scheme, opts, pl.euro, bb, tb, pl.total_tiles, res.data(), s)) != SIMR_OK) return st;
   for (const auto& grp : amer_passes(opts, pl.amer)) {
     Carve cg = cv;  // every pass reuses the same region
     AmerGroup ag = carve_amer_group(cg, opts, grp);
@@ -1355,6 +1382,16 @@ simr_status simr_price(simr_ctx* ctx, const simr_option* opt, const simr_params*
                        size_t ws_bytes, void* stream) {
   if (!opt || !out) return fail(SIMR_EINVAL, "NULL argument");
   return simr_price_batch(ctx, opt, 1, params, out, d_ws, ws_bytes, stream);
+}
+
+static simr_status noalloc_result(const simr_option& opt, const double* h, hipStream_t s, simr_result* out) {
+  SIMR_HIP(hipStreamSynchronize(s));
+  simr_result r;
+  std::memset(&r, 0, sizeof r);
+  mean_se(h[0], h[1], opt.paths, &r.price, &r.std_err);
+  r.paths = opt.paths;
+  *out = r;
+  return SIMR_OK;
 }
 
 simr_status simr_price_noalloc(simr_ctx* ctx, const simr_option* opt, const simr_params* params, simr_result* out,
@@ -1393,6 +1430,13 @@ simr_status simr_price_noalloc(simr_ctx* ctx, const simr_option* opt, const simr
   const int32_t tail[3] = {0, 0, (int32_t)ntiles};
   std::memcpy(rec + 512, tail, sizeof tail);
   char* base = ctx->scratch;
+  double* results = (double*)(base + kScratchResult);
+  double* h = ctx->noalloc_sums;  // pinned at simr_create: the copy needs no staging of its own
+  if (solo(scheme, opt->paths)) {
+    if ((st = enqueue_solo(ctx, scheme, d, block, ppl, (double*)(base + kScratchPartials), results, h, s)) != SIMR_OK)
+      return st;
+    return noalloc_result(*opt, h, s, out);
+  }
   BatchLaunch L;
   L.opts = (const DevOpt*)base;
   L.order = (const int32_t*)(base + 512);
@@ -1404,20 +1448,12 @@ simr_status simr_price_noalloc(simr_ctx* ctx, const simr_option* opt, const simr
   L.block = block;
   L.ppl = ppl;
   L.grid = grid_for(ctx, scheme, block, ppl, ntiles);
-  double* results = (double*)(base + kScratchResult);
   SIMR_HIP(launch_stage_record(rec, sizeof rec, base, s));
   SIMR_HIP(launch_reset_words(L.counter, 16, s));
   SIMR_HIP(launch_batch_price(scheme, L, s));
   SIMR_HIP(launch_finalize_rows(L.partials, 2, L.opts, 1, 0, results, s));
-  double* h = ctx->noalloc_sums;  // pinned at simr_create: the copy needs no staging of its own
   SIMR_HIP(hipMemcpyAsync(h, results, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-  SIMR_HIP(hipStreamSynchronize(s));
-  simr_result r;
-  std::memset(&r, 0, sizeof r);
-  mean_se(h[0], h[1], opt->paths, &r.price, &r.std_err);
-  r.paths = opt->paths;
-  *out = r;
-  return SIMR_OK;
+  return noalloc_result(*opt, h, s, out);
 }
 
 }  // extern "C"

@@ -74,6 +74,98 @@ __global__ __launch_bounds__(BLOCK) void batch_price_kernel(const DevOpt* __rest
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// European pricing of one option too small to fill the chip.  A step of one wave is some 110
+// instructions, 60% of them the random words and Box-Muller, which need nothing of the step before:
+// here PPL waves of a block carry one path slot each through the transitions while two more per slot draw
+// the variates of the next kSoloSteps steps into LDS, on SIMDs that would be idle.  A block takes the paths of one wave of
+// a tile of batch_price_kernel (tile lanes w * 64 + lane, slot j = wave j) and writes their two sums, which
+// solo_sum_kernel adds in that kernel's order: the same bits.  The constants come as an argument, so there
+// is no upload, and a block has one unit, so there is no queue to clear.
+//   Bound by the serial chain: 0.15 us a step (0.23 in one wave), the transition with its reads from LDS.  A call
+// of 8,192 paths x 64 steps takes 37 us in place of 50, 8 of the 13 us from the upload and the queue's reset that fell away.
+// ---------------------------------------------------------------------------------------------
+constexpr int kSoloSteps = 8;
+
+template <int SCHEME, int PPL>
+__global__ __launch_bounds__(3 * PPL * kWave) void price_solo_kernel(DevOpt o, int32_t waves_per_tile,
+                                                                     double* __restrict__ sums) {
+  __shared__ float s_draw[2][kSoloSteps][3][PPL][kWave];
+  __shared__ float s_x[PPL][kWave];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int j = wave % PPL, role = wave / PPL;  // role 0: transitions, 1 and 2: every other step's variates
+  const int32_t tile = (int32_t)blockIdx.x / waves_per_tile, w = (int32_t)blockIdx.x % waves_per_tile;
+  const uint32_t path = (uint32_t)((tile * PPL + j) * waves_per_tile + w) * kWave + lane;
+  auto produce = [&](int32_t n0, int buf) {
+#pragma unroll
+    for (int i = 0; i < kSoloSteps / 2; ++i) {
+      const int k = 2 * i + role - 1;
+      const Draw d = draw(o, (uint32_t)(n0 + k), path);  // past the last step: drawn and not read
+      s_draw[buf][k][0][j][lane] = d.z1;
+      s_draw[buf][k][1][j][lane] = d.z2;
+      s_draw[buf][k][2][j][lane] = d.u;
+    }
+  };
+  float x = 0.0f, v = o.v0;
+  if (role != 0) produce(0, 0);
+  __syncthreads();
+  for (int32_t n0 = 0, buf = 0; n0 < o.steps; n0 += kSoloSteps, buf ^= 1) {
+    if (role != 0) {
+      if (n0 + kSoloSteps < o.steps) produce(n0 + kSoloSteps, buf ^ 1);
+    } else {
+      Draw d[kSoloSteps];
+#pragma unroll
+      for (int k = 0; k < kSoloSteps; ++k)
+        d[k] = Draw{s_draw[buf][k][0][j][lane], s_draw[buf][k][1][j][lane], s_draw[buf][k][2][j][lane], 0.0f};
+#pragma unroll
+      for (int k = 0; k < kSoloSteps; ++k)
+        if (n0 + k < o.steps) transition<SCHEME>(o, x, v, d[k]);
+    }
+    __syncthreads();
+  }
+  if (role == 0) s_x[j][lane] = path < (uint32_t)o.paths ? o.disc * intrinsic(o, asset(o, x)) : 0.0f;
+  __syncthreads();
+  if (wave == 0) {
+    Kahan k1, k2;
+#pragma unroll
+    for (int q = 0; q < PPL; ++q) {  // path of slot q: slots lie a tile row apart
+      if (path + (uint32_t)(q * waves_per_tile) * kWave < (uint32_t)o.paths) {
+        const float X = s_x[q][lane];
+        k1.add(X);
+        k2.add(X * X);
+      }
+    }
+    const double a = wave_sum(k1.value()), b = wave_sum(k2.value());
+    if (lane == 0) {
+      sums[2 * (size_t)blockIdx.x] = a;
+      sums[2 * (size_t)blockIdx.x + 1] = b;
+    }
+  }
+}
+
+// The sums of price_solo_kernel's waves: a tile's in wave order, then the tiles as finalize_rows_kernel
+// adds them.  Block c: column c.
+__global__ __launch_bounds__(256) void solo_sum_kernel(const double* __restrict__ sums, int32_t waves_per_tile,
+                                                       int32_t ntiles, double* __restrict__ out) {
+  __shared__ double s[256];
+  const int32_t c = (int32_t)blockIdx.x;
+  double acc = 0.0;
+  for (int32_t t = threadIdx.x; t < ntiles; t += 256) {
+    const double* row = sums + 2 * (size_t)t * waves_per_tile + c;
+    double a = row[0];
+    for (int32_t w = 1; w < waves_per_tile; ++w) a += row[2 * w];
+    acc += a;
+  }
+  s[threadIdx.x] = acc;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[c] = s[0];
+}
+
 // Sums, for each option of `opts` (one block each), its rows [slot0, slot0 + ntiles) of a
 // row-major table of `ncol` doubles in a fixed order: thread t adds rows t, t + 256, ...
 // sequentially, then the 256 partial sums are combined by a fixed tree.  With opts == nullptr
@@ -2395,6 +2487,35 @@ hipError_t launch_batch_price(int scheme, const BatchLaunch& L, hipStream_t s) {
   if (scheme == 3) return launch_batch_s<3>(L, s);
   if (scheme == 4) return launch_batch_s<4>(L, s);
   return hipErrorInvalidValue;
+}
+
+template <int SCHEME>
+static hipError_t launch_solo_s(const DevOpt& o, int ppl, int waves_per_tile, int grid, double* sums, hipStream_t s) {
+  if (ppl == 1)
+    hipLaunchKernelGGL((price_solo_kernel<SCHEME, 1>), dim3(grid), dim3(3 * kWave), 0, s, o, waves_per_tile, sums);
+  else if (ppl == 2)
+    hipLaunchKernelGGL((price_solo_kernel<SCHEME, 2>), dim3(grid), dim3(6 * kWave), 0, s, o, waves_per_tile, sums);
+  else if (ppl == 4)
+    hipLaunchKernelGGL((price_solo_kernel<SCHEME, 4>), dim3(grid), dim3(12 * kWave), 0, s, o, waves_per_tile, sums);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_price_solo(int scheme, const DevOpt& o, int block, int ppl, double* sums, hipStream_t s) {
+  const int wpt = block / kWave;
+  if (block % kWave != 0 || wpt < 1 || o.ntiles < 1) return hipErrorInvalidValue;
+  const int grid = o.ntiles * wpt;
+  if (scheme == 0) return launch_solo_s<0>(o, ppl, wpt, grid, sums, s);
+  if (scheme == 1) return launch_solo_s<1>(o, ppl, wpt, grid, sums, s);
+  if (scheme == 2) return launch_solo_s<2>(o, ppl, wpt, grid, sums, s);
+  if (scheme == 3) return launch_solo_s<3>(o, ppl, wpt, grid, sums, s);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_solo_sum(const DevOpt& o, int block, const double* sums, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(solo_sum_kernel, dim3(2), dim3(256), 0, s, sums, (int32_t)(block / kWave), o.ntiles, out);
+  return hipGetLastError();
 }
 
 int batch_kernel_occupancy(int scheme, int block, int ppl) {

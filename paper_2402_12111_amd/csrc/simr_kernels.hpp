@@ -137,6 +137,11 @@ hipError_t launch_lsm_dates(const DevOpt& o, const float* xs, const float* vs, c
 
 hipError_t launch_batch_price(int scheme, const BatchLaunch& L, hipStream_t s);
 int batch_kernel_occupancy(int scheme, int block, int ppl);
+// One European option (schemes 0 to 3; o.ntiles tiles of block * ppl paths) with its variates drawn by
+// waves of their own: {sum X, sum X^2} per wave of a tile to sums (ntiles * block / 64 rows), then their
+// total to out.
+hipError_t launch_price_solo(int scheme, const DevOpt& o, int block, int ppl, double* sums, hipStream_t s);
+hipError_t launch_solo_sum(const DevOpt& o, int block, const double* sums, double* out, hipStream_t s);
 hipError_t launch_finalize_rows(const double* rows, int ncol, const DevOpt* opts, int nopt, int nrows, double* out,
                                 hipStream_t s);
 hipError_t launch_reset_words(uint32_t* p, int64_t n, hipStream_t s);

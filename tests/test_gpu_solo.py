@@ -1,0 +1,38 @@
+"""One small European option (variates drawn by waves of their own) against the batch kernel, bit for bit:
+the same paths and the same order of the sums, at the edges of its chunks of 8 steps, of a
+wave and of a tile, for every tile shape and scheme that has the kernel, and on both entry points."""
+import pytest
+
+from paper_2402_12111_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def S():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2402_12111_amd import simr
+    simr.library()
+    return simr
+
+
+def bits(r):
+    return r.price, r.std_err
+
+
+@pytest.mark.parametrize("tile", [(128, 1), (128, 4), (256, 1), (256, 2)])
+@pytest.mark.parametrize("scheme", [0, 1, 2, 3])
+def test_equals_the_batch_kernel(S, scheme, tile):
+    S.price(W.option(paths=64, steps=1), scheme)  # tunes the scheme, so its tile can be put back
+    old = S.get_tile()
+    try:
+        S.set_tile(*tile)
+        for paths, steps in ((2, 1), (64, 7), (65, 8), (1023, 9), (1025, 16), (5000, 17), (131072, 3), (131073, 3)):
+            o = W.option(K=101.0, payoff=steps % 2, paths=paths, steps=steps, seed=paths)
+            want = bits(S.price_batch([o, o], scheme)[1])
+            assert bits(S.price(o, scheme)) == want, (paths, steps)
+            assert bits(S.price_noalloc(o, scheme)) == want, (paths, steps)
+    finally:
+        S.set_tile(*old)
