@@ -789,6 +789,11 @@ simr_status autotune(simr_ctx* c, int scheme, const TuneBufs& tb, hipStream_t s)
 // 93.4 / 65.0; 65,536 x 252 95.5 / 81.7; 131,072 x 252 122.6 / 114.4; 196,608 x 252 152.6 / 157.4;
 // 2^19 x 252 303 / 336.
 constexpr int64_t kSoloPaths = 1 << 17;
+// The same for the checkpointing forward pass of the Greeks, which has no upload or queue to save: a call of
+// nine Greeks of 32,768 paths x 252 steps with forward_ckpt_kernel / this 223 / 198 us, of 98,304
+// 293 / 258, of 131,072 247 / 242 (two waves of paths per SIMD), where the cheap Euler step gains
+// nothing (76.2 / 76.6 for 64 steps) and the truncated Gaussian one loses 1%.
+constexpr int64_t kSoloCkptPaths = 3 << 15;
 
 bool solo(int scheme, int64_t paths) { return scheme != SIMR_SCHEME_BK && paths <= kSoloPaths; }
 
@@ -800,7 +805,7 @@ simr_status enqueue_solo(simr_ctx* c, int scheme, const DevOpt& d, int block, in
     Prof pf(c, SIMR_PROF_PRICE, s);
     SIMR_HIP(launch_price_solo(scheme, d, block, ppl, sums, s));
   }
-  SIMR_HIP(launch_solo_sum(d, block, sums, results, s));
+  SIMR_HIP(launch_solo_sum(sums, block, d.ntiles, results, s));
   SIMR_HIP(hipMemcpyAsync(host, results, sizeof(double) * 2, hipMemcpyDeviceToHost, s));
   return SIMR_OK;
 }
@@ -1507,11 +1512,20 @@ simr_status greeks_enqueue(simr_ctx* ctx, const simr_option* opt, int scheme, in
     SIMR_HIP(launch_adjoint(scheme, d, ck, ablock, ext, lb.vs + (size_t)(ck - 1) * o.paths, (size_t)ck * o.paths,
                             lb.xs, lb.tau, gb.gpart, s));
   } else {
-    {
-      Prof pf(ctx, SIMR_PROF_CKPT, s);
-      SIMR_HIP(launch_forward_ckpt(scheme, d, ck, gb.ck, gb.xN, gb.partials, s));
+    if (o.paths <= kSoloCkptPaths) {
+      // the sums per wave lie where the adjoint's rows will be (at least 18 doubles a tile, 8 taken)
+      {
+        Prof pf(ctx, SIMR_PROF_CKPT, s);
+        SIMR_HIP(launch_ckpt_solo(scheme, d, ck, gb.ck, gb.xN, gb.gpart, s));
+      }
+      SIMR_HIP(launch_solo_sum(gb.gpart, kCkBlock, gb.nblk, gb.result, s));
+    } else {
+      {
+        Prof pf(ctx, SIMR_PROF_CKPT, s);
+        SIMR_HIP(launch_forward_ckpt(scheme, d, ck, gb.ck, gb.xN, gb.partials, s));
+      }
+      SIMR_HIP(launch_finalize_rows(gb.partials, 2, nullptr, 1, gb.nblk, gb.result, s));
     }
-    SIMR_HIP(launch_finalize_rows(gb.partials, 2, nullptr, 1, gb.nblk, gb.result, s));
     Prof pf(ctx, SIMR_PROF_ADJOINT, s);
     SIMR_HIP(launch_adjoint(scheme, d, ck, ablock, ext, gb.ck, (size_t)o.paths, gb.xN, nullptr, gb.gpart, s));
   }

@@ -81,15 +81,17 @@ __global__ __launch_bounds__(BLOCK) void batch_price_kernel(const DevOpt* __rest
 // the variates of the next kSoloSteps steps into LDS, on SIMDs that would be idle.  A block takes the paths of one wave of
 // a tile of batch_price_kernel (tile lanes w * 64 + lane, slot j = wave j) and writes their two sums, which
 // solo_sum_kernel adds in that kernel's order: the same bits.  The constants come as an argument, so there
-// is no upload, and a block has one unit, so there is no queue to clear.
+// is no upload, and a block has one unit, so there is no queue to clear.  CKPT: also v at steps CK, 2 CK, ...
+// (row k - 1 of ck) and x_N, in place of forward_ckpt_kernel.
 //   Bound by the serial chain: 0.15 us a step (0.23 in one wave), the transition with its reads from LDS.  A call
 // of 8,192 paths x 64 steps takes 37 us in place of 50, 8 of the 13 us from the upload and the queue's reset that fell away.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSoloSteps = 8;
 
-template <int SCHEME, int PPL>
+template <int SCHEME, int PPL, bool CKPT>
 __global__ __launch_bounds__(3 * PPL * kWave) void price_solo_kernel(DevOpt o, int32_t waves_per_tile,
-                                                                     double* __restrict__ sums) {
+                                                                     double* __restrict__ sums, int32_t CK,
+                                                                     float* __restrict__ ck, float* __restrict__ xN) {
   __shared__ float s_draw[2][kSoloSteps][3][PPL][kWave];
   __shared__ float s_x[PPL][kWave];
   const int lane = threadIdx.x & (kWave - 1);
@@ -108,6 +110,8 @@ __global__ __launch_bounds__(3 * PPL * kWave) void price_solo_kernel(DevOpt o, i
     }
   };
   float x = 0.0f, v = o.v0;
+  int32_t next = CK;      // the next checkpoint's step
+  float* row = ck;        // and its row
   if (role != 0) produce(0, 0);
   __syncthreads();
   for (int32_t n0 = 0, buf = 0; n0 < o.steps; n0 += kSoloSteps, buf ^= 1) {
@@ -120,9 +124,21 @@ __global__ __launch_bounds__(3 * PPL * kWave) void price_solo_kernel(DevOpt o, i
         d[k] = Draw{s_draw[buf][k][0][j][lane], s_draw[buf][k][1][j][lane], s_draw[buf][k][2][j][lane], 0.0f};
 #pragma unroll
       for (int k = 0; k < kSoloSteps; ++k)
-        if (n0 + k < o.steps) transition<SCHEME>(o, x, v, d[k]);
+        if (n0 + k < o.steps) {
+          if constexpr (CKPT) {
+            if (n0 + k == next) {
+              if (path < (uint32_t)o.paths) row[path] = v;
+              next += CK;
+              row += o.paths;
+            }
+          }
+          transition<SCHEME>(o, x, v, d[k]);
+        }
     }
     __syncthreads();
+  }
+  if constexpr (CKPT) {
+    if (role == 0 && path < (uint32_t)o.paths) xN[path] = x;
   }
   if (role == 0) s_x[j][lane] = path < (uint32_t)o.paths ? o.disc * intrinsic(o, asset(o, x)) : 0.0f;
   __syncthreads();
@@ -2492,11 +2508,14 @@ hipError_t launch_batch_price(int scheme, const BatchLaunch& L, hipStream_t s) {
 template <int SCHEME>
 static hipError_t launch_solo_s(const DevOpt& o, int ppl, int waves_per_tile, int grid, double* sums, hipStream_t s) {
   if (ppl == 1)
-    hipLaunchKernelGGL((price_solo_kernel<SCHEME, 1>), dim3(grid), dim3(3 * kWave), 0, s, o, waves_per_tile, sums);
+    hipLaunchKernelGGL((price_solo_kernel<SCHEME, 1, false>), dim3(grid), dim3(3 * kWave), 0, s, o, waves_per_tile, sums,
+                       0, nullptr, nullptr);
   else if (ppl == 2)
-    hipLaunchKernelGGL((price_solo_kernel<SCHEME, 2>), dim3(grid), dim3(6 * kWave), 0, s, o, waves_per_tile, sums);
+    hipLaunchKernelGGL((price_solo_kernel<SCHEME, 2, false>), dim3(grid), dim3(6 * kWave), 0, s, o, waves_per_tile, sums,
+                       0, nullptr, nullptr);
   else if (ppl == 4)
-    hipLaunchKernelGGL((price_solo_kernel<SCHEME, 4>), dim3(grid), dim3(12 * kWave), 0, s, o, waves_per_tile, sums);
+    hipLaunchKernelGGL((price_solo_kernel<SCHEME, 4, false>), dim3(grid), dim3(12 * kWave), 0, s, o, waves_per_tile,
+                       sums, 0, nullptr, nullptr);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
@@ -2513,8 +2532,25 @@ hipError_t launch_price_solo(int scheme, const DevOpt& o, int block, int ppl, do
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_solo_sum(const DevOpt& o, int block, const double* sums, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(solo_sum_kernel, dim3(2), dim3(256), 0, s, sums, (int32_t)(block / kWave), o.ntiles, out);
+hipError_t launch_ckpt_solo(int scheme, const DevOpt& o, int ck, float* ckbuf, float* xN, double* sums, hipStream_t s) {
+  constexpr int wpt = kCkBlock / kWave;
+  if (ck < 1) return hipErrorInvalidValue;
+  const dim3 grid((o.paths + kCkBlock - 1) / kCkBlock * wpt), block(3 * kWave);
+  if (scheme == 0)
+    hipLaunchKernelGGL((price_solo_kernel<0, 1, true>), grid, block, 0, s, o, wpt, sums, ck, ckbuf, xN);
+  else if (scheme == 1)
+    hipLaunchKernelGGL((price_solo_kernel<1, 1, true>), grid, block, 0, s, o, wpt, sums, ck, ckbuf, xN);
+  else if (scheme == 2)
+    hipLaunchKernelGGL((price_solo_kernel<2, 1, true>), grid, block, 0, s, o, wpt, sums, ck, ckbuf, xN);
+  else if (scheme == 3)
+    hipLaunchKernelGGL((price_solo_kernel<3, 1, true>), grid, block, 0, s, o, wpt, sums, ck, ckbuf, xN);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_solo_sum(const double* sums, int block, int ntiles, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(solo_sum_kernel, dim3(2), dim3(256), 0, s, sums, (int32_t)(block / kWave), (int32_t)ntiles, out);
   return hipGetLastError();
 }
 

@@ -141,7 +141,9 @@ int batch_kernel_occupancy(int scheme, int block, int ppl);
 // waves of their own: {sum X, sum X^2} per wave of a tile to sums (ntiles * block / 64 rows), then their
 // total to out.
 hipError_t launch_price_solo(int scheme, const DevOpt& o, int block, int ppl, double* sums, hipStream_t s);
-hipError_t launch_solo_sum(const DevOpt& o, int block, const double* sums, double* out, hipStream_t s);
+hipError_t launch_solo_sum(const double* sums, int block, int ntiles, double* out, hipStream_t s);
+// The same for launch_forward_ckpt's outputs, with tiles of kCkBlock paths.
+hipError_t launch_ckpt_solo(int scheme, const DevOpt& o, int ck, float* ckbuf, float* xN, double* sums, hipStream_t s);
 hipError_t launch_finalize_rows(const double* rows, int ncol, const DevOpt* opts, int nopt, int nrows, double* out,
                                 hipStream_t s);
 hipError_t launch_reset_words(uint32_t* p, int64_t n, hipStream_t s);

@@ -36,3 +36,23 @@ def test_equals_the_batch_kernel(S, scheme, tile):
             assert bits(S.price_noalloc(o, scheme)) == want, (paths, steps)
     finally:
         S.set_tile(*old)
+
+
+@pytest.mark.parametrize("ck", [16, 32])
+@pytest.mark.parametrize("scheme", [0, 1, 2, 3])
+def test_greeks_on_its_checkpoints(S, scheme, ck):
+    """The Greeks' price is the call's alone, and their values do not depend on where the checkpoints
+    lie but for the order of the sums (1e-5 of each Greek's scale; a wrong checkpoint is off by its size)."""
+    S.price(W.option(paths=64, steps=1), scheme)
+    old = S.get_tile()
+    try:
+        S.set_tile(256, 1)
+        for paths, steps in ((2, 1), (65, 8), (1023, 9), (1025, 32), (5000, 65), (98304, 17), (98305, 17)):
+            o = W.option(K=101.0, payoff=1, paths=paths, steps=steps, seed=paths)
+            g = S.greeks(o, scheme, checkpoint_every=ck)
+            h = S.greeks(o, scheme, checkpoint_every=8)
+            assert bits(g) == bits(S.price(o, scheme)), (paths, steps)
+            for a, b, se in zip(g.grads, h.grads, h.grad_se):
+                assert abs(a - b) <= 1e-5 * max(abs(b), se * paths ** 0.5), (paths, steps, a, b)
+    finally:
+        S.set_tile(*old)
