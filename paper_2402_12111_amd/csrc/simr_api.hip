@@ -785,14 +785,13 @@ simr_status autotune(simr_ctx* c, int scheme, const TuneBufs& tb, hipStream_t s)
 
 // One option of at most this many paths is priced by price_solo_kernel: from two waves of paths per
 // SIMD on, the drawing waves no longer find idle issue slots, and LDS is extra work.  Measured (us per call,
-// batch kernel with its upload, queue and sums / this): 8,192 paths x 64 steps 50.5 / 37.1, x 252
-// 93.4 / 65.0; 65,536 x 252 95.5 / 81.7; 131,072 x 252 122.6 / 114.4; 196,608 x 252 152.6 / 157.4;
-// 2^19 x 252 303 / 336.
+// batch kernel with its upload, queue and sums / this): 8,192 paths x 64 steps 50.5 / 37.5, x 252
+// 93.4 / 65.1; 65,536 x 252 95.5 / 65.6; 131,072 x 252 122.6 / 104.9; 196,608 x 252 149.2 / 155.0;
+// 2^19 x 252 295 / 329.
 constexpr int64_t kSoloPaths = 1 << 17;
-// The same for the checkpointing forward pass of the Greeks, which has no upload or queue to save: a call of
-// nine Greeks of 32,768 paths x 252 steps with forward_ckpt_kernel / this 223 / 198 us, of 98,304
-// 293 / 258, of 131,072 247 / 242 (two waves of paths per SIMD), where the cheap Euler step gains
-// nothing (76.2 / 76.6 for 64 steps) and the truncated Gaussian one loses 1%.
+// The same for the checkpointing forward pass of the Greeks, which has no upload or queue to save: nine
+// Greeks x 252 steps with forward_ckpt_kernel / this, 32,768 paths 215 / 183 us, 65,536 218 / 204,
+// 98,304 278 / 250, 131,072 241 / 232 (QE) and 267 / 275 (martingale-corrected), 196,608 303 / 309.
 constexpr int64_t kSoloCkptPaths = 3 << 15;
 
 bool solo(int scheme, int64_t paths) { return scheme != SIMR_SCHEME_BK && paths <= kSoloPaths; }

@@ -84,7 +84,8 @@ __global__ __launch_bounds__(BLOCK) void batch_price_kernel(const DevOpt* __rest
 // is no upload, and a block has one unit, so there is no queue to clear.  CKPT: also v at steps CK, 2 CK, ...
 // (row k - 1 of ck) and x_N, in place of forward_ckpt_kernel.
 //   Bound by the serial chain: 0.15 us a step (0.23 in one wave), the transition with its reads from LDS.  A call
-// of 8,192 paths x 64 steps takes 37 us in place of 50, 8 of the 13 us from the upload and the queue's reset that fell away.
+// of 8,192 paths x 64 steps takes 37 us in place of 50, 8 of the 13 us from the upload and the queue's reset that
+// fell away.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSoloSteps = 8;
 
@@ -112,6 +113,8 @@ __global__ __launch_bounds__(3 * PPL * kWave) void price_solo_kernel(DevOpt o, i
   float x = 0.0f, v = o.v0;
   int32_t next = CK;      // the next checkpoint's step
   float* row = ck;        // and its row
+  // the block waits for the transitions: they issue first (65,536 paths x 252 steps 81.7 -> 65.6 us)
+  if (role == 0) __builtin_amdgcn_s_setprio(3);
   if (role != 0) produce(0, 0);
   __syncthreads();
   for (int32_t n0 = 0, buf = 0; n0 < o.steps; n0 += kSoloSteps, buf ^= 1) {
