@@ -839,6 +839,22 @@ simr_status run_euro_batch(simr_ctx* c, int scheme, const simr_option* opts, con
     slot += (int32_t)ntile[k];
     order[k] = (int32_t)k;
   }
+  double* res_host = (double*)(up + res_off);
+  auto collect = [&]() -> simr_status {
+    SIMR_HIP(hipStreamSynchronize(s));
+    for (int64_t k = 0; k < m; ++k) {
+      simr_result r;
+      std::memset(&r, 0, sizeof r);
+      mean_se(res_host[2 * k], res_host[2 * k + 1], opts[idx[k]].paths, &r.price, &r.std_err);
+      r.paths = opts[idx[k]].paths;
+      out[idx[k]] = r;
+    }
+    return SIMR_OK;
+  };
+  if (m == 1 && solo(scheme, opts[idx[0]].paths)) {  // not captured: the launch holds the option's constants
+    if ((st = enqueue_solo(c, scheme, dopt[0], block, ppl, tb.partials, b.results, res_host, s)) != SIMR_OK) return st;
+    return collect();
+  }
   std::stable_sort(order, order + m, [&](int32_t a, int32_t bq) {
     const double ca = (double)opts[idx[a]].steps * (double)opts[idx[a]].paths;
     const double cb = (double)opts[idx[bq]].steps * (double)opts[idx[bq]].paths;
@@ -848,7 +864,6 @@ simr_status run_euro_batch(simr_ctx* c, int scheme, const simr_option* opts, con
   for (int64_t k = 0; k < m; ++k) uprefix[k + 1] = uprefix[k] + (int32_t)ntile[order[k]];
   const int32_t nunits = uprefix[m];
   if ((int64_t)nunits != total_tiles) return fail(SIMR_EINVAL, "internal: unit count mismatch");
-  double* res_host = (double*)(up + res_off);
 
   BatchLaunch L;
   L.opts = b.opts;
@@ -874,11 +889,7 @@ simr_status run_euro_batch(simr_ctx* c, int scheme, const simr_option* opts, con
     return SIMR_OK;
   };
 
-  const bool captured = s != nullptr && !c->prof_on;
-  if (!captured && m == 1 && solo(scheme, opts[idx[0]].paths)) {
-    // (a captured launch would keep the constants of the option it was captured with)
-    if ((st = enqueue_solo(c, scheme, dopt[0], block, ppl, tb.partials, b.results, res_host, s)) != SIMR_OK) return st;
-  } else if (captured) {
+  if (s != nullptr && !c->prof_on) {
     auto key = std::make_tuple((uintptr_t)b.upload, (uintptr_t)c->pinned, (int)m, (int)nunits, block, ppl, scheme,
                                L.grid, (uintptr_t)s);
     auto it = c->graphs.find(key);
@@ -906,15 +917,7 @@ simr_status run_euro_batch(simr_ctx* c, int scheme, const simr_option* opts, con
     simr_status es = enqueue();
     if (es != SIMR_OK) return es;
   }
-  SIMR_HIP(hipStreamSynchronize(s));
-  for (int64_t k = 0; k < m; ++k) {
-    simr_result r;
-    std::memset(&r, 0, sizeof r);
-    mean_se(res_host[2 * k], res_host[2 * k + 1], opts[idx[k]].paths, &r.price, &r.std_err);
-    r.paths = opts[idx[k]].paths;
-    out[idx[k]] = r;
-  }
-  return SIMR_OK;
+  return collect();
 }
 
 // Pinned staging of one American pass: the task table, then the results read back (2 doubles

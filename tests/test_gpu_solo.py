@@ -56,3 +56,16 @@ def test_greeks_on_its_checkpoints(S, scheme, ck):
                 assert abs(a - b) <= 1e-5 * max(abs(b), se * paths ** 0.5), (paths, steps, a, b)
     finally:
         S.set_tile(*old)
+
+
+def test_on_a_stream_with_new_constants_each_call(S):
+    """On a stream of its own the small option is launched, not replayed: options of one shape and other
+    constants give the default stream's results."""
+    import torch
+    opts = [W.option(K=95.0 + k, xi=0.2 + 0.1 * k, paths=3000, steps=19, seed=k) for k in range(4)]
+    want = [bits(S.price(o)) for o in opts]
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        assert [bits(S.price(o)) for o in opts] == want
+        assert [bits(S.price(o)) for o in reversed(opts)] == want[::-1]
+    st.synchronize()
