@@ -201,7 +201,8 @@ simr_status simr_price(simr_ctx* ctx, const simr_option* opt, const simr_params*
  * held from the library's first use on that GPU until the process ends),
  * whose address simr_create records: the option record, the work-queue
  * counter (cleared by a kernel on every call), one {sum X, sum X^2} pair per
- * path tile and the result sums.  Limits: European options only (American
+ * path tile (an option of at most 131,072 paths needs only pairs, one per wave
+ * of a tile) and the result sums.  Limits: European options only (American
  * ones return SIMR_EUNSUPPORTED), and at most 131,072 path tiles, i.e.
  * 131,072 x (block x paths per lane) paths at the context's tile (33,554,432
  * at the untuned default 256 x 1); larger options return SIMR_EINVAL with
@@ -228,7 +229,10 @@ simr_status simr_price_noalloc(simr_ctx* ctx, const simr_option* opt, const simr
  * count, tile total, tile, scheme, grid, stream) and replayed by later calls
  * of that shape with the new options' contents; on the NULL stream, which
  * cannot be captured, or while profiling, the same launches are enqueued
- * directly (the results are the same bit for bit).  American
+ * directly (the results are the same bit for bit).  A lone European option of
+ * at most 131,072 paths (every scheme but the exact one) is launched directly
+ * on any stream, without upload or queue, by a kernel of its own with the same
+ * results bit for bit.  American
  * options are processed in passes of consecutive options (in the caller's
  * order) whose buffers fit 8 GiB together, or one alone if it needs more: the
  * forward passes and regression pre-passes of a pass run back to back, and

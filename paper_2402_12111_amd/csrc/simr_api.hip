@@ -136,7 +136,7 @@ struct Carve {
 //   [512, 524)    the queue order {0} and unit prefix {0, tiles}
 //   [1024, 1088)  the queue counter (16 words, cleared by a kernel before every launch)
 //   [1280, 1296)  the result sums {sum X, sum X^2}
-//   [2048, ...)   {sum X, sum X^2} per path tile, kScratchTiles tiles
+//   [2048, ...)   {sum X, sum X^2} per path tile, kScratchTiles tiles (one small option: per wave of a tile)
 // ---------------------------------------------------------------------------------------------
 constexpr int64_t kScratchTiles = 131072;
 constexpr size_t kScratchRecord = 512 + 3 * sizeof(int32_t);
@@ -796,14 +796,9 @@ constexpr int64_t kSoloCkptPaths = 3 << 15;
 
 bool solo(int scheme, int64_t paths) { return scheme != SIMR_SCHEME_BK && paths <= kSoloPaths; }
 
-// Prices `o` (constants `d`, tile as tuned) and leaves {sum X, sum X^2} in `host` once the stream
-// is synchronised; `sums` holds two doubles per wave of a tile, at most kSoloPaths / 64 + 4 waves.
-simr_status enqueue_solo(simr_ctx* c, int scheme, const DevOpt& d, int block, int ppl, double* sums, double* results,
-                         double* host, hipStream_t s) {
-  {
-    Prof pf(c, SIMR_PROF_PRICE, s);
-    SIMR_HIP(launch_price_solo(scheme, d, block, ppl, sums, s));
-  }
+// After launch_price_solo: its sums per wave of a tile (at most kSoloPaths / 64 + 3 rows of two doubles)
+// become {sum X, sum X^2} in `host` once the stream is synchronised.
+simr_status solo_sums(const DevOpt& d, int block, const double* sums, double* results, double* host, hipStream_t s) {
   SIMR_HIP(launch_solo_sum(sums, block, d.ntiles, results, s));
   SIMR_HIP(hipMemcpyAsync(host, results, sizeof(double) * 2, hipMemcpyDeviceToHost, s));
   return SIMR_OK;
@@ -852,7 +847,11 @@ simr_status run_euro_batch(simr_ctx* c, int scheme, const simr_option* opts, con
     return SIMR_OK;
   };
   if (m == 1 && solo(scheme, opts[idx[0]].paths)) {  // not captured: the launch holds the option's constants
-    if ((st = enqueue_solo(c, scheme, dopt[0], block, ppl, tb.partials, b.results, res_host, s)) != SIMR_OK) return st;
+    {
+      Prof pf(c, SIMR_PROF_PRICE, s);
+      SIMR_HIP(launch_price_solo(scheme, dopt[0], block, ppl, tb.partials, s));
+    }
+    if ((st = solo_sums(dopt[0], block, tb.partials, b.results, res_host, s)) != SIMR_OK) return st;
     return collect();
   }
   std::stable_sort(order, order + m, [&](int32_t a, int32_t bq) {
@@ -1440,8 +1439,9 @@ simr_status simr_price_noalloc(simr_ctx* ctx, const simr_option* opt, const simr
   double* results = (double*)(base + kScratchResult);
   double* h = ctx->noalloc_sums;  // pinned at simr_create: the copy needs no staging of its own
   if (solo(scheme, opt->paths)) {
-    if ((st = enqueue_solo(ctx, scheme, d, block, ppl, (double*)(base + kScratchPartials), results, h, s)) != SIMR_OK)
-      return st;
+    double* sums = (double*)(base + kScratchPartials);
+    SIMR_HIP(launch_price_solo(scheme, d, block, ppl, sums, s));
+    if ((st = solo_sums(d, block, sums, results, h, s)) != SIMR_OK) return st;
     return noalloc_result(*opt, h, s, out);
   }
   BatchLaunch L;

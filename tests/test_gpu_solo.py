@@ -1,6 +1,8 @@
 """One small European option (variates drawn by waves of their own) against the batch kernel, bit for bit:
 the same paths and the same order of the sums, at the edges of its chunks of 8 steps, of a
 wave and of a tile, for every tile shape and scheme that has the kernel, and on both entry points."""
+import ctypes
+
 import pytest
 
 from paper_2402_12111_amd import workloads as W
@@ -69,3 +71,28 @@ def test_on_a_stream_with_new_constants_each_call(S):
         assert [bits(S.price(o)) for o in opts] == want
         assert [bits(S.price(o)) for o in reversed(opts)] == want[::-1]
     st.synchronize()
+
+
+def test_profiling_records_price_and_not_the_allocation_free_call(S):
+    """While profiling, a small price records its kernel; the allocation-free call creates no events."""
+    L, ctx = S.library(), S.context()
+    L.simr_profile_enable.argtypes = [ctypes.c_void_p, ctypes.c_int]
+    L.simr_profile_read.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.POINTER(ctypes.c_double),
+                                    ctypes.POINTER(ctypes.c_int64)]
+    L.simr_profile_reset.argtypes = [ctypes.c_void_p]
+    o = W.option(paths=3000, steps=9)
+    want = bits(S.price(o))
+
+    def launches():
+        ms, n = ctypes.c_double(), ctypes.c_int64()
+        assert L.simr_profile_read(ctx, 0, ctypes.byref(ms), ctypes.byref(n)) == 0
+        return n.value
+
+    L.simr_profile_reset(ctx)
+    L.simr_profile_enable(ctx, 1)
+    try:
+        assert bits(S.price_noalloc(o)) == want and launches() == 0
+        assert bits(S.price(o)) == want and launches() == 1
+    finally:
+        L.simr_profile_enable(ctx, 0)
+        L.simr_profile_reset(ctx)
