@@ -2064,7 +2064,8 @@ __device__ __forceinline__ float qe_reverse(const DevOpt& o, float v, float V, f
   constexpr bool MG = KIND == 1;
   // log-price step: x' = x + c0 + K1 v + K2 V + sqrt(K3 v + K4 V) Z2
   const float w = __builtin_fmaf(o.K3, v, o.K4 * V);
-  const float q = (w > 0.0f) ? xbar * z2 * 0.5f * rsq(w) : 0.0f;
+  // v_rsq_f32 of a subnormal is infinite; the forward pass's v_sqrt_f32 of one is 0, like its derivative here
+  const float q = (w >= 0x1p-126f) ? xbar * z2 * 0.5f * rsq(w) : 0.0f;
   a.K1 = __builtin_fmaf(xbar, v, a.K1);
   a.K2 = __builtin_fmaf(xbar, V, a.K2);
   a.K3 = __builtin_fmaf(q, v, a.K3);
