@@ -2072,7 +2072,7 @@ BasketBufs carve_basket(Carve& cv, const simr_basket& b, int op, int num_cus) {
   u.ao = u.upload ? (DevOpt*)(u.upload + u.off_opts) : nullptr;
   u.task = u.upload ? (LsmTask*)(u.upload + u.off_task) : nullptr;
   u.dl = (u.upload && op == 3) ? (float*)(u.upload + u.off_dl) : nullptr;
-  for (int m = 0; m < 3; ++m) u.lay[m] = basket_layout(m, d, P, num_cus);
+  for (int m = 0; m < 3; ++m) u.lay[m] = basket_layout(m, d, P, N, num_cus);
   u.nblk = u.lay[0].blocks;
   u.nchunk = (int)((P + kBasketChunk - 1) / kBasketChunk);
   u.rows = cv.take<double>((size_t)u.nblk * 2);

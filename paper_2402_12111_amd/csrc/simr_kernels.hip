@@ -8,6 +8,7 @@
 // longstaffSchwartzPathReduction is the per-date regression reduction: wave64 shuffles, an
 // LDS tree, FP64 cross-block sums and an FP64 solve in the last block to finish.
 #include <algorithm>
+#include <climits>
 #include <cstring>
 
 #include "simr_device.hpp"
@@ -3408,10 +3409,36 @@ __global__ __launch_bounds__(256) void basket_wave_kernel(const DevBasket* __res
   constexpr int Q0 = LEAFA == A ? 0 : DMAX;                 // a row: the assets' pairs (none if a lane is a leaf),
   constexpr int SS = LEAVES ? Q0 + LEAVES + (LEAVES + 3) / 4 * 2 : DMAX;  // the leaves' and the leaf quads'
   static_assert(LEAVES == 0 || (LEAVES % 4 == 0 && LEAVES <= DMIN / A + 1 + DMAX * (LEAFA == A)), "a lane per leaf");
+  // The constants of short runs of few paths (LEAFA != 0) pass through the LDS that the sums take over
+  // afterwards: a lane reading its own asset's from memory makes some 80 uncoalesced loads a wave, longer
+  // than a step (32 assets, 65,536 paths x 1 step 247 -> 229 us a call).
+  constexpr bool STAGED = LEAFA != 0;
+  constexpr int TRI = DMAX * (DMAX + 1) / 2;
+  struct Constants {
+    DevOpt o[DMAX];
+    float L[TRI], Li[MODE == 1 ? TRI : 1];
+  };
+  constexpr int SUMS = 4 * ROWS * SS, STAGE = STAGED ? (int)(sizeof(Constants) / sizeof(float2)) + 1 : 0;
   __shared__ __align__(16) float s_z[4][ROWS * ZS];
-  __shared__ __align__(16) float2 s_s[4][ROWS * SS];
+  __shared__ __align__(16) float2 s_s[SUMS > STAGE ? SUMS : STAGE];
   const DevBasket& B = *bk;
   const int d = B.d;
+  const DevOpt* from_o = ao;
+  const float *from_L = B.L, *from_Li = B.Linv;
+  if constexpr (STAGED) {
+    Constants& c = *reinterpret_cast<Constants*>(s_s);
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(ao);
+    uint32_t* dst = reinterpret_cast<uint32_t*>(c.o);
+    for (int q = threadIdx.x; q < d * (int)(sizeof(DevOpt) / sizeof(uint32_t)); q += 256) dst[q] = src[q];
+    for (int q = threadIdx.x; q < tri(d); q += 256) {
+      c.L[q] = B.L[q];
+      if constexpr (MODE == 1) c.Li[q] = B.Linv[q];
+    }
+    __syncthreads();
+    from_o = c.o;
+    from_L = c.L;
+    from_Li = c.Li;
+  }
   if constexpr (MODE == 2) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nzero; i += (int64_t)gridDim.x * 256) zero[i] = 0u;
   }
@@ -3423,7 +3450,7 @@ __global__ __launch_bounds__(256) void basket_wave_kernel(const DevBasket* __res
   const size_t P = (size_t)B.paths;
   const bool live = pl < PPW && p < (uint32_t)B.paths;
   float* zrow = s_z[wid] + pl * ZS;
-  float2* srow = s_s[wid] + pl * SS;
+  float2* srow = s_s + (wid * ROWS + pl) * SS;
   const int i0 = sub * A;
   DevOpt o[A];
   float Lr[A][DMAX], Li[MODE == 1 ? A : 1][MODE == 1 ? DMAX : 1], wS0[A];
@@ -3433,7 +3460,7 @@ __global__ __launch_bounds__(256) void basket_wave_kernel(const DevBasket* __res
   for (int j = 0; j < A; ++j) {
     has[j] = i0 + j < d && pl < PPW;
     const int i = has[j] ? i0 + j : 0;  // lanes without an asset step asset 0 and are not read
-    o[j] = ao[i];
+    o[j] = from_o[i];
     wS0[j] = has[j] ? B.wS0[i] : 0.0f;
     x[j] = 0.0f;
     v[j] = o[j].v0;
@@ -3441,10 +3468,11 @@ __global__ __launch_bounds__(256) void basket_wave_kernel(const DevBasket* __res
     sb[j] = 0.0f;
 #pragma unroll
     for (int k = 0; k < DMAX; ++k) {
-      Lr[j][k] = k <= i ? B.L[tri(i) + (k <= i ? k : 0)] : 0.0f;
-      if constexpr (MODE == 1) Li[j][k] = k >= i && k < d ? B.Linv[tri(k) + i] : 0.0f;
+      Lr[j][k] = k <= i ? from_L[tri(i) + (k <= i ? k : 0)] : 0.0f;
+      if constexpr (MODE == 1) Li[j][k] = k >= i && k < d ? from_Li[tri(k) + i] : 0.0f;
     }
   }
+  if constexpr (STAGED) __syncthreads();  // before the sums overwrite the constants
   for (int q = sub; q < ZS; q += L) zrow[q] = 0.0f;
   for (int q = sub; q < SS; q += L) srow[q] = make_float2(0.0f, 0.0f);
   wave_fence();
@@ -3718,18 +3746,38 @@ static int basket_order(int d, int64_t paths, int num_cus) {
   return most;
 }
 
-BasketLayout basket_layout(int mode, int d, int64_t paths, int num_cus) {
+BasketLayout basket_layout(int mode, int d, int64_t paths, int steps, int num_cus) {
   BasketLayout l;
   const int lpp = basket_order(d, paths, num_cus);
   l.leaf = lpp > 1 ? basket_tier(d) / lpp : 0;
-  // The wave kernel up to this many waves per SIMD at one path per lane, where it and one path per
-  // lane measured the same.  us per call, one path per lane / wave: 8 assets x 252 steps, 131,072
-  // paths: Greeks 1,362 / 786; 262,144 x 63: 550 / 447, write-out and induction 796 / 771; 2^20 x 20:
-  // 645 / 622 and 734 / 780.  The write-out sums the basket every step, in asset order from 2 waves
-  // per SIMD on, one lane per path at work: 20 assets, 131,072 paths x 50 965 / 1,023, 262,144 x 30
-  // 855 / 1,091.  32 assets, 262,144 x 10: price 471 / 507, Greeks 1,259 / 1,122.
-  const int64_t limit = mode == 2 ? (d <= 8 ? 8 : 2) : mode == 1 ? 8 : (d <= 16 ? 8 : 4);
-  if (d >= 3 && (paths + kWave - 1) / kWave < limit * 4 * (int64_t)num_cus) l.per_lane = d <= 8 || l.leaf == 1 ? 1 : 2;
+  // The wave kernel by waves per SIMD at one path per lane, and steps: its waves hold few paths, so setting
+  // them up (and, in a price, summing them up) weighs more, the more of them there are, the fewer steps they
+  // take and the more lanes are idle.  Each line lies where the two measured the same.
+  // us per call, one path per lane / wave: 8 assets x 252 steps, 131,072 paths: Greeks 1,362 / 786; 32 assets,
+  // 460,000 paths: Greeks x 3 1,157 / 1,329, x 12 2,414 / 1,906; 12 assets, 200,000: Greeks x 3 169 / 176, x 12
+  // 273 / 234; prices: 5 assets, 131,072 x 3 46 / 49, x 12 69 / 64; 16 assets (no lane idle), 460,000 x 1
+  // 101 / 164, x 25 629 / 554; 9 assets (10 of 64 idle) 262,144 x 12 132 / 145, x 100 742 / 741, 390,000 x 50
+  // 525 / 558.  The write-out sums the basket every step, in asset order one lane per path at work: 6 assets,
+  // 200,000 x 25 325 / 302, 390,000 x 25 406 / 419; 20 assets, 131,072 x 50 965 / 1,023.  Baskets whose sums
+  // are not in asset order have this kernel only, and at 1 or 2 steps that costs them: 26 assets, 110,000 x 1
+  // took 167 us with several lanes per path and all constants in LDS, and takes 189.
+  const int64_t waves = (paths + kWave - 1) / kWave, full = 4 * (int64_t)num_cus;
+  const int A = d <= 8 ? 1 : 2, used = kWave / ((d + A - 1) / A) * d / A;  // lanes with an asset, in its last step
+  constexpr int kNever = INT_MAX;
+  int least = 1;  // steps
+  if (l.leaf != 0) {
+    // the only kernel with these sums
+  } else if (d < 3 || (mode == 2 && d > 8) || waves >= 8 * full) {
+    least = kNever;
+  } else if (waves >= 4 * full) {
+    least = mode == 2 || (mode == 0 && d > 16) ? kNever : mode == 1 ? (d > 16 || used >= 60 ? 12 : 18) : 25 + 6 * (kWave - used);
+  } else if (waves >= 2 * full) {
+    least = mode == 1 && d <= 16 ? 6 : mode == 0 && d > 16 && used < 58 ? 18 : 12;
+  } else if (waves >= full) {
+    least = mode == 1 ? 3 : 6;
+  }
+  const bool wave = steps >= least;
+  if (wave) l.per_lane = d <= 8 || l.leaf == 1 ? 1 : 2;
   int per_block = 256;
   if (l.per_lane) per_block = 4 * (kWave / ((d + l.per_lane - 1) / l.per_lane));
   l.blocks = (int)((paths + per_block - 1) / per_block);

@@ -204,7 +204,7 @@ int basket_tier(int d);
 // after another (0), or in leaves of `leaf` assets, then pairwise.  per_lane: 0, one path per lane
 // (leaf = 0); or the assets per lane of the wave kernel.  blocks: of 256 threads.
 struct BasketLayout { int leaf = 0, per_lane = 0, blocks = 0; };
-BasketLayout basket_layout(int mode, int d, int64_t paths, int num_cus);
+BasketLayout basket_layout(int mode, int d, int64_t paths, int steps, int num_cus);
 // mode 0 price, 1 Greeks records, 2 Longstaff-Schwartz write-out (see basket_path_kernel); rows: 2
 // doubles per block of the layout.
 hipError_t launch_basket_paths(int scheme, int mode, int d, int64_t paths, const BasketLayout& l, const DevBasket* bk,
