@@ -1,7 +1,7 @@
 """Which basket kernel runs, by assets, paths and steps (on 256 CUs), and that each is right there: one path per lane
 from 524,288 paths on, or fewer with few steps, and for American baskets of more than 8 assets from 131,072;
 one or two assets per lane otherwise, the basket summed in asset order from 131,072 paths on and for up to
-8 assets.  Prices and Greeks against the oracle; terminal values of the two kernels on
+8 assets.  Prices, Greeks and exercise policies against the oracle; terminal values of the two kernels on
 both sides of each limit bit for bit."""
 import numpy as np
 import pytest
@@ -34,6 +34,24 @@ def check_greeks(S, b):
     assert abs(g.price - price) <= 1e-4 * b0(b)
     assert np.all(np.abs(np.array(g.delta) - delta) <= 1e-4 * np.maximum(np.abs(delta), scale * delta_se))
     assert np.all(np.abs(np.array(g.gamma) - gamma) <= 1e-4 * np.maximum(np.abs(gamma), scale * gamma_se))
+
+
+@pytest.mark.parametrize("d", [4, 8, 12, 20])
+def test_greeks_one_path_per_lane(S, d):
+    check_greeks(S, W.basket(d, seed=d, paths=1 << 19, steps=2))
+
+
+@pytest.mark.parametrize("d", [12, 20])
+def test_greeks_of_many_assets_summed_in_asset_order(S, d):
+    check_greeks(S, W.basket(d, seed=d, paths=140000, steps=12))
+
+
+@pytest.mark.parametrize("d", [12, 20])
+def test_write_out_of_many_assets_one_path_per_lane(S, d):
+    b = W.basket(d, seed=d, moneyness=1.1, payoff=W.AMER_PUT, paths=140000, steps=4)
+    g, tau, _ = S.debug_basket_lsm(b)
+    value = oracle.basket_stopped_values(oracle.Basket(**b), tau).mean()
+    assert abs(g.price - max(value, 0.1 * b0(b))) <= 1e-4 * b0(b)
 
 
 @pytest.mark.parametrize("d,paths,steps", [(5, 70000, (1, 5, 6)), (5, 140000, (11, 12)), (20, 140000, (11, 12)),
