@@ -459,7 +459,9 @@ simr_status simr_debug_basket_lsm(simr_ctx* ctx, const simr_basket* b, const sim
  * layout that holds more options co-resident (two options of 2^20 paths fit one launch only on
  * 256-thread blocks; options of up to 64 blocks take blocks with a wave of their own for the
  * exchange).  An option's paths per block, not the layout, fix its summation
- * order, so modes 0, 3 and 4 give the same bits. */
+ * order, so modes 0, 3 and 4 give the same bits.
+ * mode 5 is mode 0 with the check that an option's blocks share an XCD made to fail: options placed on
+ * one then exchange through memory, with the same bits. */
 simr_status simr_set_lsm_launch(simr_ctx* ctx, int32_t mode, int32_t grid_max);
 
 /* Host-side fault injection, a test of the error paths (no kernel is affected).  Arms the

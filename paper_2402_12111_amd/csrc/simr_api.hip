@@ -169,6 +169,7 @@ struct simr_ctx {
   int lsm_grid_max = 64;       // largest cooperative grid of the backward induction
   int lsm_block = 0;           // its block size: 0 chosen per launch, or fixed at 1024 or 256
   bool lsm_per_date = false;   // force one launch per date instead of the cooperative kernel
+  int lsm_far_test = 0;        // 1: options placed on one XCD are made to look spread
   bool lsm_fail_test = false;  // mark the exchange as failed before each cooperative induction
   int tile_block[5] = {0, 0, 0, 0, 0};  // per scheme: 0 = not chosen yet
   int tile_ppl[5] = {0, 0, 0, 0, 0};
@@ -1002,6 +1003,7 @@ simr_status enqueue_american_group(simr_ctx* c, int scheme, const simr_option* o
     t.block0 = at[k].block0;
     t.nblocks = coop ? at[k].nblocks : b.nblk;
     t.xcd = at[k].xcd;
+    t.xcd_skew = c->lsm_far_test;
     t.gram = b.gram;
     t.rdt = o.r * o.T / o.steps;
     t.chunks = lsm_gram_chunks(o.paths);
@@ -1256,13 +1258,15 @@ simr_status simr_profile_reset(simr_ctx* ctx) {
 
 simr_status simr_set_lsm_launch(simr_ctx* ctx, int32_t mode, int32_t grid_max) {
   if (!ctx) return fail(SIMR_EINVAL, "ctx is NULL");
-  if (mode < 0 || mode > 4)
+  if (mode < 0 || mode > 5)
     return fail(SIMR_EINVAL, "mode must be 0 (cooperative), 1 (one launch per date), 2 (failure test), 3 "
-                             "(cooperative on 256-thread blocks) or 4 (cooperative on 1024-thread blocks)");
+                             "(cooperative on 256-thread blocks), 4 (cooperative on 1024-thread blocks) "
+                             "or 5 (placement test)");
   if (grid_max < 0) return fail(SIMR_EINVAL, "grid_max must be >= 0");
   ctx->lsm_per_date = mode == 1;
   ctx->lsm_fail_test = mode == 2;
   ctx->lsm_block = mode == 3 ? 256 : mode == 4 ? 1024 : 0;
+  ctx->lsm_far_test = mode == 5 ? 1 : 0;
   if (grid_max > 0) ctx->lsm_grid_max = grid_max;
   return SIMR_OK;
 }
@@ -2174,6 +2178,7 @@ simr_status basket_american_run(simr_ctx* c, int scheme, const simr_basket& b, c
   t.block0 = at[0].block0;
   t.nblocks = coop ? at[0].nblocks : (int)((b.paths + kLsmBlock - 1) / kLsmBlock);
   t.xcd = at[0].xcd;
+  t.xcd_skew = c->lsm_far_test;
   simr_status st = basket_upload(c, scheme, b, u, &t, s);
   if (st != SIMR_OK) return st;
   int32_t* flags = (int32_t*)(u.zero + 1);

@@ -1078,6 +1078,11 @@ constexpr uint32_t kSpinLimit = 1u << 22;  // passes (a few seconds of polling) 
 // the readers' agent-scope loads find it (a store at workgroup scope writes through the L1, and an
 // agent-scope load misses it); otherwise it goes on to memory, where blocks of other XCDs look.
 // A round of 25 or 32 blocks that only exchange takes 0.65 us near and 1.28 us through memory.
+//   The memory model does not promise this: a workgroup-scope store need not become visible to other
+// workgroups.  It rests on how gfx950 carries the two accesses out -- no store stops short of the L2,
+// and blocks with the same HW_REG_XCC_ID have the same L2 -- which is why the placement is checked on
+// every run, by stores at agent scope.  A word read early or never seen cannot pass for a sum (its tag
+// is the date), and the wait is bounded, so a failure would be an error and not a price.
 template <int NB>
 __device__ __forceinline__ void xchg_store(SIMR_GLOBAL unsigned long long* slot, int word, float value, uint32_t k,
                                            bool near) {
@@ -1239,9 +1244,9 @@ __device__ __forceinline__ int32_t task_of_induction_block(const LsmTask* __rest
 // writes only after every block has left this wait.  Called by one wave; at most one poller's rows.
 template <int XW, int NB>
 __device__ __forceinline__ bool task_on_one_xcd(SIMR_GLOBAL unsigned long long* xchg, uint32_t blk, uint32_t G,
-                                                int32_t* status) {
+                                                int32_t skew, int32_t* status) {
   const int lane = threadIdx.x & (kWave - 1);
-  const float x = (float)(__builtin_amdgcn_s_getreg(kHwRegXccId) & 15);
+  const float x = (float)((__builtin_amdgcn_s_getreg(kHwRegXccId) & 15) + skew * (int)blk);
   xchg_store<NB>(xchg + (size_t)blk * XW, lane, lane == 0 ? x : lane == 1 ? x * x : 0.0f, kXcdTag, false);
   const double y = xchg_gather<XW, NB>(xchg, G, 0, kXcdTag, status);
   const double s1 = readlane_d(y, 0), s2 = readlane_d(y, kWave / XW);
@@ -1542,7 +1547,7 @@ __global__ __launch_bounds__(BLOCK + kWave, relay_waves(PPL, NB)) void lsm_relay
     SIMR_GLOBAL unsigned long long* mine = xchg + (size_t)blk * LL::kXW;
     const SIMR_GLOBAL double* __restrict__ fac = as_global((const double*)T.fac);
     double* beta64 = T.beta64;
-    const bool near = T.xcd >= 0 && N >= 2 && task_on_one_xcd<LL::kXW, NB>(xchg, blk, G, status);
+    const bool near = T.xcd >= 0 && N >= 2 && task_on_one_xcd<LL::kXW, NB>(xchg, blk, G, T.xcd_skew, status);
     double mrow[NB], grow, mvalid;
     auto request = [&](int32_t n) {  // lane i < NB: row i of the date's M; e^{r n dt}; the valid flag
       const SIMR_GLOBAL double* rec = fac + (size_t)n * LL::kRec;
@@ -2733,7 +2738,7 @@ struct CoopFit {
 CoopFit coop_fit(const std::vector<int>& nblocks, int block, int ppl, bool relay, int cap, int num_cus, int rows) {
   CoopFit f{block, ppl, relay};
   const size_t n = nblocks.size();
-  if (relay && num_cus % kXcds == 0) {
+  if (relay && num_cus == 32 * kXcds) {  // the whole chip: on a partition of it options are spread
     int used[kXcds] = {};
     // alone, and two or more paths per virtual lane: sharing its XCD's CUs costs what the nearer
     // exchange gains (131,072 paths: 507 us near, 496 spread; 65,536 paths 424 and 459)

@@ -58,6 +58,7 @@ struct LsmTask {
   int32_t* flags;            // SIMR_LSM_FEW_ITM | SIMR_LSM_DROPPED of the option (read by the finish)
   int32_t block0, nblocks;   // its first block and their count (of the induction)
   int32_t xcd;               // >= 0: block b of the task is block (block0 + b) kXcds + xcd of the launch
+  int32_t xcd_skew;          // 1: block b reports its XCD's number plus b, so that they look spread (a test); else 0
   // the batched launches over all tasks of a pass (spill, Gram pre-pass, factors, adjoints):
   // task t's blocks [first, first + count) of each
   float* gram;               // Gram sums of every (date, chunk)
@@ -120,7 +121,7 @@ hipError_t launch_spill_tasks(int scheme, const LsmTask* tasks, int ntasks, int 
 hipError_t launch_gram_tasks(const LsmTask* tasks, int ntasks, int grid, hipStream_t s);
 // (every option of at most 2^18 paths, so a date's Gram rows are at most 64)
 hipError_t launch_factor_tasks(const LsmTask* tasks, int ntasks, int dates, hipStream_t s);
-// tasks: device array, sorted by block0, block0 relative to this launch.
+// tasks: device array of the launch's options in any order, block0 relative to this launch.
 hipError_t launch_lsm_coop(const LsmTask* tasks, int ntasks, const LsmLaunchSet& ls, int32_t* status, hipStream_t s,
                            int nb = 6);
 // out[2 t], out[2 t + 1] = sums of task t's block partials in block order (FP64); then, as int32
