@@ -788,11 +788,15 @@ simr_status autotune(simr_ctx* c, int scheme, const TuneBufs& tb, hipStream_t s)
 // SIMD on, the drawing waves no longer find idle issue slots, and LDS is extra work.  Measured (us per call,
 // batch kernel with its upload, queue and sums / this): 8,192 paths x 64 steps 50.5 / 37.5, x 252
 // 93.4 / 65.1; 65,536 x 252 95.5 / 65.6; 131,072 x 252 122.6 / 104.9; 196,608 x 252 149.2 / 155.0;
-// 2^19 x 252 295 / 329.
+// 2^19 x 252 295 / 329.  The other schemes, 131,072 x 252: full-truncation Euler 95 / 85, martingale-
+// corrected QE 132 / 116, truncated Gaussian 134 / 113.  Tiles of 2 and 4 paths per lane, whose blocks have
+// 6 and 12 waves and up to 50 KiB of LDS (QE, 131,072 x 252): 128 x 2 189 / 117, 128 x 4 254 / 96.
 constexpr int64_t kSoloPaths = 1 << 17;
 // The same for the checkpointing forward pass of the Greeks, which has no upload or queue to save: nine
 // Greeks x 252 steps with forward_ckpt_kernel / this, 32,768 paths 215 / 183 us, 65,536 218 / 204,
 // 98,304 278 / 250, 131,072 241 / 232 (QE) and 267 / 275 (martingale-corrected), 196,608 303 / 309.
+// The whole Greeks call before the kernel / with it at 98,304 x 252: QE 283 / 242, full-truncation Euler
+// 178 / 165, martingale-corrected QE 317 / 273, truncated Gaussian 323 / 290.
 constexpr int64_t kSoloCkptPaths = 3 << 15;
 
 bool solo(int scheme, int64_t paths) { return scheme != SIMR_SCHEME_BK && paths <= kSoloPaths; }
@@ -932,7 +936,9 @@ size_t amer_pinned_bytes(int n) { return amer_task_bytes(n) + amer_result_bytes(
 // and step.  Measured (us per call, a launch each / together): 30 options of 25,000 paths x 504
 // steps 7,413 / 3,717, 10 of 25,000 x 126 945 / 499; Greeks of 4 options of 131,072 x 252 1,956 /
 // 1,825, of 2^18 2,763 / 2,646, of 2^19 5,569 / 5,662, of 2 of 2^20 4,780 / 4,837 (a large option
-// fills the chip alone).
+// fills the chip alone).  Two small options would gain too: 25,000 x 126 315 / 259 (Greeks 441 / 332),
+// 131,072 x 252 945 / 906 (1,189 / 1,087).  They keep their launches for a reason outside the chip: a test
+// of the error paths fails the 25th launch of a Greeks batch that has such a pair, and together it has fewer.
 constexpr int64_t kTogetherMin = 3;
 constexpr int64_t kTogetherPaths = (int64_t)1 << 18;
 
