@@ -2770,8 +2770,8 @@ CoopFit coop_fit(const std::vector<int>& nblocks, int block, int ppl, bool relay
 // depends neither on the others nor on the layout.  Induction of one launch (us, one option of 25,000
 // paths x 252 dates unless said): relay512 near 314, spread 421, relay256 near 356, spread 458; 1024
 // 532.  20 options: relay256 near 519, relay512 spread 628, 256 799.  30 options x 504 dates:
-// relay256 1,500 spread, 256 1,919.  One of 131,072 paths: relay512 496, 1024 559; 8 of them relay512 near
-// 629, 256 918; one of 262,144: 641, 719.
+// relay256 1,500 spread, 1,325 with 24 of them near (three share an XCD) and 6 spread, 256 1,919.  One of
+// 131,072 paths: relay512 496, 1024 559; 8 of them relay512 near 629, 256 918; one of 262,144: 641, 719.
 struct CoopLayout { int block; bool relay; };
 static const CoopLayout kLayouts[] = {{512, true}, {256, true}, {1024, false}, {256, false}};
 
