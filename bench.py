@@ -85,7 +85,7 @@ TRAFFIC_BYTES = {
 }
 VALU_ISSUE_QUADS = {
     ('forward_spill', 1048576, 252): 2.9299e+08,
-    ('lsm_gram', 1048576, 252): 1.2889e+08,
+    ('lsm_gram', 1048576, 252): 1.2890e+08,
     ('lsm_backward', 1048576, 252): 4.6179e+08,
     ('adjoint', 1048576, 252): 2.3368e+08,
     ('forward_spill', 131072, 252): 3.8004e+07,
