@@ -3416,33 +3416,28 @@ __global__ __launch_bounds__(256) void basket_wave_kernel(const DevBasket* __res
   static_assert(LEAVES == 0 || (LEAVES % 4 == 0 && LEAVES <= DMIN / A + 1 + DMAX * (LEAFA == A)), "a lane per leaf");
   // The constants of short runs of few paths (LEAFA != 0) pass through the LDS that the sums take over
   // afterwards: a lane reading its own asset's from memory makes some 80 uncoalesced loads a wave, longer
-  // than a step (32 assets, 65,536 paths x 1 step 247 -> 229 us a call).
+  // than a step (32 assets, 80,000 paths x 1 step 260 -> 229 us a call).
   constexpr bool STAGED = LEAFA != 0;
-  constexpr int TRI = DMAX * (DMAX + 1) / 2;
-  struct Constants {
+  struct Constants {  // rows of L, and columns of L^{-1}, with their zeros
+    float L[DMAX][ZS], Li[MODE == 1 ? DMAX : 1][ZS];
     DevOpt o[DMAX];
-    float L[TRI], Li[MODE == 1 ? TRI : 1];
   };
   constexpr int SUMS = 4 * ROWS * SS, STAGE = STAGED ? (int)(sizeof(Constants) / sizeof(float2)) + 1 : 0;
   __shared__ __align__(16) float s_z[4][ROWS * ZS];
   __shared__ __align__(16) float2 s_s[SUMS > STAGE ? SUMS : STAGE];
   const DevBasket& B = *bk;
   const int d = B.d;
-  const DevOpt* from_o = ao;
-  const float *from_L = B.L, *from_Li = B.Linv;
+  Constants& c = *reinterpret_cast<Constants*>(s_s);
   if constexpr (STAGED) {
-    Constants& c = *reinterpret_cast<Constants*>(s_s);
     const uint32_t* src = reinterpret_cast<const uint32_t*>(ao);
     uint32_t* dst = reinterpret_cast<uint32_t*>(c.o);
     for (int q = threadIdx.x; q < d * (int)(sizeof(DevOpt) / sizeof(uint32_t)); q += 256) dst[q] = src[q];
-    for (int q = threadIdx.x; q < tri(d); q += 256) {
-      c.L[q] = B.L[q];
-      if constexpr (MODE == 1) c.Li[q] = B.Linv[q];
+    for (int q = threadIdx.x; q < d * DMAX; q += 256) {
+      const int i = q / DMAX, k = q % DMAX;
+      c.L[i][k] = k <= i ? B.L[tri(i) + (k <= i ? k : 0)] : 0.0f;
+      if constexpr (MODE == 1) c.Li[i][k] = k >= i && k < d ? B.Linv[tri(k) + i] : 0.0f;
     }
     __syncthreads();
-    from_o = c.o;
-    from_L = c.L;
-    from_Li = c.Li;
   }
   if constexpr (MODE == 2) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nzero; i += (int64_t)gridDim.x * 256) zero[i] = 0u;
@@ -3465,16 +3460,34 @@ __global__ __launch_bounds__(256) void basket_wave_kernel(const DevBasket* __res
   for (int j = 0; j < A; ++j) {
     has[j] = i0 + j < d && pl < PPW;
     const int i = has[j] ? i0 + j : 0;  // lanes without an asset step asset 0 and are not read
-    o[j] = from_o[i];
+    o[j] = STAGED ? c.o[i] : ao[i];
     wS0[j] = has[j] ? B.wS0[i] : 0.0f;
     x[j] = 0.0f;
     v[j] = o[j].v0;
     sa[j] = 0.0f;
     sb[j] = 0.0f;
+    if constexpr (STAGED) {
 #pragma unroll
-    for (int k = 0; k < DMAX; ++k) {
-      Lr[j][k] = k <= i ? from_L[tri(i) + (k <= i ? k : 0)] : 0.0f;
-      if constexpr (MODE == 1) Li[j][k] = k >= i && k < d ? from_Li[tri(k) + i] : 0.0f;
+      for (int k0 = 0; k0 < DMAX; k0 += 4) {
+        const float4 t = *reinterpret_cast<const float4*>(&c.L[i][k0]);
+        Lr[j][k0] = t.x;
+        Lr[j][k0 + 1] = t.y;
+        Lr[j][k0 + 2] = t.z;
+        Lr[j][k0 + 3] = t.w;
+        if constexpr (MODE == 1) {
+          const float4 u = *reinterpret_cast<const float4*>(&c.Li[i][k0]);
+          Li[j][k0] = u.x;
+          Li[j][k0 + 1] = u.y;
+          Li[j][k0 + 2] = u.z;
+          Li[j][k0 + 3] = u.w;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < DMAX; ++k) {
+        Lr[j][k] = k <= i ? B.L[tri(i) + (k <= i ? k : 0)] : 0.0f;
+        if constexpr (MODE == 1) Li[j][k] = k >= i && k < d ? B.Linv[tri(k) + i] : 0.0f;
+      }
     }
   }
   if constexpr (STAGED) __syncthreads();  // before the sums overwrite the constants
@@ -3765,7 +3778,7 @@ BasketLayout basket_layout(int mode, int d, int64_t paths, int steps, int num_cu
   // 525 / 558.  The write-out sums the basket every step, in asset order one lane per path at work: 6 assets,
   // 200,000 x 25 325 / 302, 390,000 x 25 406 / 419; 20 assets, 131,072 x 50 965 / 1,023.  Baskets whose sums
   // are not in asset order have this kernel only, and at 1 or 2 steps that costs them: 26 assets, 110,000 x 1
-  // took 167 us with several lanes per path and all constants in LDS, and takes 189.
+  // took 169 us with several lanes per path and all constants in LDS, and takes 187.
   const int64_t waves = (paths + kWave - 1) / kWave, full = 4 * (int64_t)num_cus;
   const int A = d <= 8 ? 1 : 2, used = kWave / ((d + A - 1) / A) * d / A;  // lanes with an asset, in its last step
   constexpr int kNever = INT_MAX;
