@@ -71,28 +71,28 @@ ALL_GROUPS = (1 << len(GROUPS)) - 1
 #    for each pair the SIMD issued together (gfx950 co-issues, e.g., v_bitop3_b32 beside an FMA).
 # They describe the kernel sources whose digest is given and are reported only while the sources
 # match.  At 2^20 paths one induction launch carries two options (the large risk run's pairs).
-TRAFFIC_SOURCES_DIGEST = "b6a8b02af9c52bc8"
+TRAFFIC_SOURCES_DIGEST = "105f75f45e4c4b27"
 TRAFFIC_BYTES = {
     ('forward_spill', 1048576, 252): 2.1140e+09,
     ('lsm_gram', 1048576, 252): 2.1097e+09,
-    ('lsm_backward', 1048576, 252): 4.3078e+09,
+    ('lsm_backward', 1048576, 252): 4.3080e+09,
     ('adjoint', 1048576, 252): 1.3996e+08,
     ('forward_spill', 131072, 252): 2.6431e+08,
     ('lsm_gram', 131072, 252): 2.6380e+08,
-    ('lsm_backward', 131072, 252): 2.8002e+08,
+    ('lsm_backward', 131072, 252): 2.7984e+08,
     ('adjoint', 131072, 252): 1.8000e+07,
-    ('price', 'c3'): 2.5131e+07,
+    ('price', 'c3'): 2.5093e+07,
 }
 VALU_ISSUE_QUADS = {
     ('forward_spill', 1048576, 252): 2.9299e+08,
-    ('lsm_gram', 1048576, 252): 1.2890e+08,
-    ('lsm_backward', 1048576, 252): 4.6179e+08,
-    ('adjoint', 1048576, 252): 2.3368e+08,
-    ('forward_spill', 131072, 252): 3.8004e+07,
-    ('lsm_gram', 131072, 252): 1.4688e+07,
+    ('lsm_gram', 1048576, 252): 1.2875e+08,
+    ('lsm_backward', 1048576, 252): 4.6201e+08,
+    ('adjoint', 1048576, 252): 2.3365e+08,
+    ('forward_spill', 131072, 252): 3.7994e+07,
+    ('lsm_gram', 131072, 252): 1.4237e+07,
     ('lsm_backward', 131072, 252): 2.5429e+07,
     ('adjoint', 131072, 252): 3.3628e+07,
-    ('price', 'c3'): 2.3138e+10,
+    ('price', 'c3'): 2.3139e+10,
 }
 # Issue quad-cycles per second of the chip: 256 CUs x 4 SIMDs x 2.4 GHz / 4.  A plain stream of
 # independent v_fma_f32 reaches 0.90 of it on this GPU.
